@@ -501,6 +501,7 @@ struct Layout {
     std::vector<int64_t> partial_off;   // per vertex: byte offset of its partial slabs (-1: none)
     std::vector<int> split;             // per vertex: extra slabs per aggIdx from a split row reduction or contraction (1: none)
     std::vector<int> split_label;       // contraction: the contracted label that is cut `split` times finer
+    std::vector<char> whole;            // per vertex: runs in its whole_vertex form
     std::vector<int64_t> aux_off;       // per vertex: byte offset of a launch's own scratch (the one-pass attention's mask classes; -1: none)
     int64_t total = 0;
 };
@@ -557,7 +558,7 @@ private:
     int64_t top_ = 0;
 };
 
-static int dry_route(const eg_graph *g, int vertex, Routed &r);
+static int dry_route(const eg_graph *g, const Vertex &v, Routed &r);
 
 // ------------------------------------------------------------------------------------------------
 // fusion of softmax chains (Section 3 of the paper writes softmax as four EinSums)
@@ -830,17 +831,41 @@ static bool merges_aggregation(const eg_graph *g, int i)
     return kind == EG_KERNEL_CONTRACT_MFMA || kind == EG_KERNEL_CONTRACT_ALU;
 }
 
-// the vertex as the merged kernel call sees it: contracted labels in one piece, one tuple per output block
-static Vertex merged_vertex(const Vertex &v)
+static Vertex unplanned_copy(const Vertex &v)
 {
     Vertex m;
     m.dtype = v.dtype; m.bound = v.bound; m.spec = v.spec; m.lx = v.lx; m.ly = v.ly; m.lz = v.lz;
     m.labels = v.labels; m.lbound = v.lbound; m.d = v.d; m.agg = v.agg;
     m.otimes = v.otimes; m.oplus = v.oplus; m.alpha = v.alpha; m.in[0] = v.in[0]; m.in[1] = v.in[1]; m.n_in = v.n_in;
+    return m;
+}
+
+// the vertex as the merged kernel call sees it: contracted labels in one piece, one tuple per output block
+static Vertex merged_vertex(const Vertex &v)
+{
+    Vertex m = unplanned_copy(v);
     for (int a : v.agg) m.d[a] = 1;
     m.plan.n_tuples = v.plan.n_tuples / v.plan.n_agg;
     m.plan.n_agg = 1;
     m.plan.n_groups = m.plan.n_tuples;
+    m.plan.valid = true;
+    return m;
+}
+
+// A vertex's execution form: cuts of labels that are not aggregated are views only, and the values of an output do not depend
+// on them (its reduction runs over the same elements in the same order), so the join walks the blocks of such labels as one
+// index space.  Tiles then straddle block borders instead of being padded at every one of them: 8192 x 4096 x 11008 cut eight
+// ways along its columns is 43 whole tile columns instead of 8 x 6 with each block's last one three eighths full (664 -> 643 us),
+// heads cut eight ways are one batch (scores of 4 x 32 heads of 2048 x 2048: 403 -> 385 us), distances of 8192 x 1024 x 8192
+// cut 2 x 2 x 2 12.99 -> 12.79 ms.  The cuts of aggregated labels stay: their partial blocks are added in order.
+static Vertex whole_vertex(const Vertex &v)
+{
+    Vertex m = unplanned_copy(v);
+    for (int l = 0; l < (int)m.d.size(); l++)
+        if (std::find(v.agg.begin(), v.agg.end(), l) == v.agg.end()) m.d[l] = 1;
+    m.plan.n_tuples = v.plan.n_agg;
+    m.plan.n_agg = v.plan.n_agg;
+    m.plan.n_groups = 1;
     m.plan.valid = true;
     return m;
 }
@@ -869,16 +894,25 @@ static int contraction_split(const Vertex &v, const ContractParams &cp, int *lab
 // the vertex with one contracted label cut c times finer
 static Vertex refined_vertex(const Vertex &v, int label, int c)
 {
-    Vertex m;
-    m.dtype = v.dtype; m.bound = v.bound; m.spec = v.spec; m.lx = v.lx; m.ly = v.ly; m.lz = v.lz;
-    m.labels = v.labels; m.lbound = v.lbound; m.d = v.d; m.agg = v.agg;
-    m.otimes = v.otimes; m.oplus = v.oplus; m.alpha = v.alpha; m.in[0] = v.in[0]; m.in[1] = v.in[1]; m.n_in = v.n_in;
+    Vertex m = unplanned_copy(v);
     m.d[label] *= c;
     m.plan.n_tuples = v.plan.n_tuples * c;
     m.plan.n_agg = v.plan.n_agg * c;
     m.plan.n_groups = v.plan.n_groups;
     m.plan.valid = true;
     return m;
+}
+
+// Whether vertex i runs in its whole_vertex form (returned in w): contractions whose blocks and whole tensors both suit the
+// kernel the blocks would run on.
+static bool takes_whole(const eg_graph *g, const Vertex &v, Vertex &w)
+{
+    if (v.n_in != 2 || v.agg.empty() || v.plan.n_groups <= 1) return false;
+    w = whole_vertex(v);
+    Routed a, b;
+    if (dry_route(g, w, a) != EG_OK || (a.kind != EG_KERNEL_CONTRACT_MFMA && a.kind != EG_KERNEL_CONTRACT_ALU)) return false;
+    if (dry_route(g, v, b) != EG_OK || b.kind != a.kind) return true;
+    return contract_dma_eligible(a.cp) || !contract_dma_eligible(b.cp);
 }
 
 static Layout make_layout(const eg_graph *g)
@@ -890,6 +924,7 @@ static Layout make_layout(const eg_graph *g)
     L.split.assign(nv, 1);
     L.split_label.assign(nv, -1);
     L.aux_off.assign(nv, -1);
+    L.whole.assign(nv, 0);
     // a fused chain runs where its last vertex stands: it reads the chain's outside operands there and writes the
     // result (and the row statistics that are still wanted); the other tensors of the chain never exist
     const std::vector<FuseGroup> groups = find_fusions(g);
@@ -932,10 +967,13 @@ static Layout make_layout(const eg_graph *g)
         if (!v.is_output) L.result_off[i] = arena.alloc(numel(v.bound) * dtype_size(v.dtype));
         {
             Routed r;
-            if (dry_route(g, i, r) == EG_OK) {
+            Vertex w;
+            const bool whole = takes_whole(g, v, w);
+            if (whole) L.whole[i] = 1;
+            if (dry_route(g, whole ? w : v, r) == EG_OK) {
                 if (r.kind == EG_KERNEL_REDUCE_ROW) L.split[i] = r.rp.split;
                 else if ((r.kind == EG_KERNEL_CONTRACT_MFMA || r.kind == EG_KERNEL_CONTRACT_ALU) && !merges_aggregation(g, i))
-                    L.split[i] = contraction_split(v, r.cp, &L.split_label[i]);
+                    L.split[i] = contraction_split(whole ? w : v, r.cp, &L.split_label[i]);
             }
         }
         const int64_t n_agg = merges_aggregation(g, i) ? 1 : v.plan.n_agg;
@@ -959,9 +997,8 @@ using namespace eg;
 
 // Routing of a vertex with dense row-major operands (what einsum_graph_plan reports and what the workspace
 // layout assumes).
-int eg::dry_route(const eg_graph *g, int vertex, Routed &r)
+int eg::dry_route(const eg_graph *g, const Vertex &v, Routed &r)
 {
-    const Vertex &v = g->v[vertex];
     static char dummy_buf[64];
     void *aligned = (void *)(((uintptr_t)dummy_buf + 15) & ~(uintptr_t)15);
     Operand X, Y;
@@ -975,7 +1012,9 @@ int eg::dry_route(const eg_graph *g, int vertex, Routed &r)
 int eg_route_vertex(const eg_graph *g, int vertex)
 {
     Routed r;
-    if (dry_route(g, vertex, r) != EG_OK) return EG_KERNEL_NONE;
+    Vertex w;
+    const Vertex &v = g->v[vertex];
+    if (dry_route(g, takes_whole(g, v, w) ? w : v, r) != EG_OK) return EG_KERNEL_NONE;
     return r.kind;
 }
 
@@ -1388,8 +1427,11 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
         s.vertex = i;
         const bool merged = merges_aggregation(g, i);
         const bool refined = !merged && L.split_label[i] >= 0 && L.split[i] > 1;
-        const Vertex vm = merged ? merged_vertex(v) : refined ? refined_vertex(v, L.split_label[i], L.split[i]) : Vertex();
-        const Vertex &vr = merged || refined ? vm : v;   // what is routed: the vertex, its merged form, or its finer cut
+        // what is routed: the vertex, with the cuts that are views only taken out, then its merged form or its finer cut
+        const Vertex vw = L.whole[i] ? whole_vertex(v) : Vertex();
+        const Vertex &vb = L.whole[i] ? vw : v;
+        const Vertex vm = merged ? merged_vertex(vb) : refined ? refined_vertex(vb, L.split_label[i], L.split[i]) : Vertex();
+        const Vertex &vr = merged || refined ? vm : vb;
         Operand X = operand_of(v.in[0]), Y;
         if (v.n_in > 1) Y = operand_of(v.in[1]);
         Operand Z = operand_of(i);
@@ -1413,8 +1455,20 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
             zstride = Z.stride;
         }
         int rc = route(vr, X, v.n_in > 1 ? &Y : nullptr, zstride, out, s.r, refined ? 1 : L.split[i]);
-        if (rc) return rc;
         const Vertex *routed = &vr;
+        Vertex vc;
+        if (L.whole[i] && (rc || s.r.kind == EG_KERNEL_GENERIC || (s.r.kind == EG_KERNEL_CONTRACT_MFMA && !contract_dma_eligible(s.r.cp)))) {
+            // the bound relations' strides may suit the blocks only
+            vc = merged ? merged_vertex(v) : refined ? refined_vertex(v, L.split_label[i], L.split[i]) : v;
+            Routed blocks;
+            const int rb = route(vc, X, v.n_in > 1 ? &Y : nullptr, zstride, out, blocks, refined ? 1 : L.split[i]);
+            if (rb == EG_OK && (rc || blocks.kind == EG_KERNEL_CONTRACT_ALU || (blocks.kind == EG_KERNEL_CONTRACT_MFMA && (s.r.kind == EG_KERNEL_GENERIC || contract_dma_eligible(blocks.cp))))) {
+                rc = rb;
+                s.r = blocks;
+                routed = &vc;
+            }
+        }
+        if (rc) return rc;
         if (merged && s.r.kind != EG_KERNEL_CONTRACT_MFMA && s.r.kind != EG_KERNEL_CONTRACT_ALU)
             return fail(EG_ERR_LIMIT, "vertex %d: the bound relations' strides leave no contraction kernel for the merged aggregation; turn tr_set_fused_aggregation off", i);
         if (L.split[i] > 1 && s.r.kind != EG_KERNEL_REDUCE_ROW &&
