@@ -827,8 +827,9 @@ static bool merges_aggregation(const eg_graph *g, int i)
 {
     const Vertex &v = g->v[i];
     if (!g->agg_in_kernel || v.is_input || v.n_in != 2 || v.plan.n_agg <= 1) return false;
-    const int kind = eg_route_vertex(g, i);
-    return kind == EG_KERNEL_CONTRACT_MFMA || kind == EG_KERNEL_CONTRACT_ALU;
+    // by the blocks' own route: relations whose strides suit only a kernel outside the contractions are accepted
+    Routed r;
+    return dry_route(g, v, r) == EG_OK && (r.kind == EG_KERNEL_CONTRACT_MFMA || r.kind == EG_KERNEL_CONTRACT_ALU);
 }
 
 static Vertex unplanned_copy(const Vertex &v)
