@@ -146,12 +146,13 @@ static bool vec_ok(const StridedDims &dims, int which, int vd, int vec, const vo
 // ------------------------------------------------------------------------------------------------
 // contraction eligibility and parameter construction
 // ------------------------------------------------------------------------------------------------
-static bool build_contract(const Vertex &v, const LabelInfo &li, const Operand &X, const Operand &Y, ContractParams &cp)
+// ragged: operands need no whole or aligned 16-byte vectors (each still contiguous along one label)
+static bool build_contract(const Vertex &v, const LabelInfo &li, const Operand &X, const Operand &Y, ContractParams &cp, bool ragged = false)
 {
     if (v.n_in != 2 || (v.oplus != EG_AGG_SUM && v.oplus != EG_AGG_MAX)) return false;
     if (X.dtype != Y.dtype) return false;
-    const int epc = X.dtype == EG_BF16 ? 8 : 4;
-    if (!aligned16(X.ptr) || !aligned16(Y.ptr)) return false;
+    const int epc = ragged ? 1 : X.dtype == EG_BF16 ? 8 : 4;
+    if (!ragged && (!aligned16(X.ptr) || !aligned16(Y.ptr))) return false;
     std::vector<int> gb, gm, gn, gk;
     for (int l = 0; l < li.nl; l++) {
         const bool x = li.inx[l], y = li.iny[l], z = li.inz[l];
@@ -241,6 +242,8 @@ static bool build_contract(const Vertex &v, const LabelInfo &li, const Operand &
         cp.span_x += (li.ext[l] - 1) * li.sx[l];
         cp.span_y += (li.ext[l] - 1) * li.sy[l];
     }
+    cp.ragged = ragged ? 1 : 0;
+    cp.wide = ragged && !(X.dtype == EG_BF16 && v.dtype == EG_BF16) ? 1 : 0;
     cp.in_dtype = X.dtype;
     cp.otimes = v.otimes;
     cp.oplus = v.oplus;
@@ -255,6 +258,7 @@ static bool build_contract(const Vertex &v, const LabelInfo &li, const Operand &
 // ------------------------------------------------------------------------------------------------
 struct Routed {
     int kind = EG_KERNEL_NONE;
+    bool ragged = false;           // contraction: on the ragged form of the kernels
     bool swapped = false;          // contraction: X and Y changed places (see route)
     ContractParams cp;
     MapParams mp;
@@ -370,9 +374,30 @@ static int route(const Vertex &v, const Operand &X, const Operand *Y, const std:
         r.cp.out = out;
         r.cp.n_tuples = n_tuples;
         r.swapped = swap;
+        r.ragged = false;
         r.kind = v.otimes == EG_MUL && v.oplus == EG_AGG_SUM ? EG_KERNEL_CONTRACT_MFMA : EG_KERNEL_CONTRACT_ALU;
         return EG_OK;
     }
+
+    // The same with operands that are no whole 16-byte vectors.  Fewer outputs than a tile, and reductions shorter than one
+    // matrix step, stay on the reductions and the one-output-per-lane kernel below, which cut a long reduction into pieces.
+    // Other scalar functions need 64 tiles of 128 x 128: a tile is some 0.9 us of vector work per contracted element whatever
+    // the number of tiles, and one output per lane is level with 30 of them (1059 x 273 x 184, 18 tiles: 975 us against 587).
+    auto suits_tiles = [&](const ContractParams &c) {
+        if (c.K < 16) return false;
+        if (v.otimes == EG_MUL && v.oplus == EG_AGG_SUM) return c.M * c.N * c.n_batch * n_tuples >= 4096;
+        return (c.M + 127) / 128 * ((c.N + 127) / 128) * c.n_batch * n_tuples >= 64;
+    };
+    if (binary && build_contract(v, lc, swap ? *Y : X, swap ? X : *Y, r.cp, true) && suits_tiles(r.cp)) {
+        r.cp.ts = tc;
+        r.cp.out = out;
+        r.cp.n_tuples = n_tuples;
+        r.swapped = swap;
+        r.ragged = true;
+        r.kind = v.otimes == EG_MUL && v.oplus == EG_AGG_SUM ? EG_KERNEL_CONTRACT_MFMA : EG_KERNEL_CONTRACT_ALU;
+        return EG_OK;
+    }
+    r.ragged = false;
 
     // output and reduction index spaces
     std::vector<int> zl(v.lz.begin(), v.lz.end());
@@ -832,6 +857,14 @@ static bool merges_aggregation(const eg_graph *g, int i)
     return dry_route(g, v, r) == EG_OK && (r.kind == EG_KERNEL_CONTRACT_MFMA || r.kind == EG_KERNEL_CONTRACT_ALU);
 }
 
+// Merged vertices whose blocks are ragged run on whatever kernel the bound relations leave them; the others are refused
+// relations that leave no 16-byte contraction kernel.
+static bool merges_ragged(const eg_graph *g, int i)
+{
+    Routed r;
+    return dry_route(g, g->v[i], r) == EG_OK && r.ragged;
+}
+
 static Vertex unplanned_copy(const Vertex &v)
 {
     Vertex m;
@@ -913,6 +946,7 @@ static bool takes_whole(const eg_graph *g, const Vertex &v, Vertex &w)
     Routed a, b;
     if (dry_route(g, w, a) != EG_OK || (a.kind != EG_KERNEL_CONTRACT_MFMA && a.kind != EG_KERNEL_CONTRACT_ALU)) return false;
     if (dry_route(g, v, b) != EG_OK || b.kind != a.kind) return true;
+    if (a.ragged || b.ragged) return b.ragged;
     return contract_dma_eligible(a.cp) || !contract_dma_eligible(b.cp);
 }
 
@@ -973,7 +1007,7 @@ static Layout make_layout(const eg_graph *g)
             if (whole) L.whole[i] = 1;
             if (dry_route(g, whole ? w : v, r) == EG_OK) {
                 if (r.kind == EG_KERNEL_REDUCE_ROW) L.split[i] = r.rp.split;
-                else if ((r.kind == EG_KERNEL_CONTRACT_MFMA || r.kind == EG_KERNEL_CONTRACT_ALU) && !merges_aggregation(g, i))
+                else if (!r.ragged && (r.kind == EG_KERNEL_CONTRACT_MFMA || r.kind == EG_KERNEL_CONTRACT_ALU) && !merges_aggregation(g, i))
                     L.split[i] = contraction_split(whole ? w : v, r.cp, &L.split_label[i]);
             }
         }
@@ -1458,19 +1492,19 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
         int rc = route(vr, X, v.n_in > 1 ? &Y : nullptr, zstride, out, s.r, refined ? 1 : L.split[i]);
         const Vertex *routed = &vr;
         Vertex vc;
-        if (L.whole[i] && (rc || s.r.kind == EG_KERNEL_GENERIC || (s.r.kind == EG_KERNEL_CONTRACT_MFMA && !contract_dma_eligible(s.r.cp)))) {
+        if (L.whole[i] && (rc || s.r.ragged || s.r.kind == EG_KERNEL_GENERIC || (s.r.kind == EG_KERNEL_CONTRACT_MFMA && !contract_dma_eligible(s.r.cp)))) {
             // the bound relations' strides may suit the blocks only
             vc = merged ? merged_vertex(v) : refined ? refined_vertex(v, L.split_label[i], L.split[i]) : v;
             Routed blocks;
             const int rb = route(vc, X, v.n_in > 1 ? &Y : nullptr, zstride, out, blocks, refined ? 1 : L.split[i]);
-            if (rb == EG_OK && (rc || blocks.kind == EG_KERNEL_CONTRACT_ALU || (blocks.kind == EG_KERNEL_CONTRACT_MFMA && (s.r.kind == EG_KERNEL_GENERIC || contract_dma_eligible(blocks.cp))))) {
+            if (rb == EG_OK && (rc || (!blocks.ragged && blocks.kind == EG_KERNEL_CONTRACT_ALU) || (!blocks.ragged && blocks.kind == EG_KERNEL_CONTRACT_MFMA && (s.r.ragged || s.r.kind == EG_KERNEL_GENERIC || contract_dma_eligible(blocks.cp))))) {
                 rc = rb;
                 s.r = blocks;
                 routed = &vc;
             }
         }
         if (rc) return rc;
-        if (merged && s.r.kind != EG_KERNEL_CONTRACT_MFMA && s.r.kind != EG_KERNEL_CONTRACT_ALU)
+        if (merged && !merges_ragged(g, i) && (s.r.ragged || (s.r.kind != EG_KERNEL_CONTRACT_MFMA && s.r.kind != EG_KERNEL_CONTRACT_ALU)))
             return fail(EG_ERR_LIMIT, "vertex %d: the bound relations' strides leave no contraction kernel for the merged aggregation; turn tr_set_fused_aggregation off", i);
         if (L.split[i] > 1 && s.r.kind != EG_KERNEL_REDUCE_ROW &&
             !(refined && (s.r.kind == EG_KERNEL_CONTRACT_MFMA || s.r.kind == EG_KERNEL_CONTRACT_ALU))) {

@@ -75,6 +75,8 @@ struct ContractParams {
     int32_t force_waves;          // 0: the launcher chooses; 4 / 8: waves per workgroup of the 256 x 256 direct-to-LDS kernel
     int32_t tile_order;           // 1: partial slabs are written tile after tile in the accumulators' order (see AggTilesParams)
     int32_t k_stages;             // filled by the launcher of the direct-to-LDS kernel: stages per output tile
+    int32_t ragged;               // 1: extents, strides or addresses are no whole 16-byte vectors; the register-staged kernels' ragged form
+    int32_t wide;                 // ragged products of 32-bit results: summed in 64 bits
     int32_t k_align;              // filled by that launcher: 0: a tile's stages start at its block's first k; 1 / 2: on the 128-byte line of X / Y below it
 };
 

@@ -8,28 +8,36 @@
 // transposed in registers on its way into LDS, so the MFMA feed is identical for every layout.
 // fp32 accumulation; the epilogue either writes fp32 partial blocks (slab aggIdx) or casts once to the
 // vertex dtype.
+//
+// Ragged operands (extents, strides or addresses that are no whole 16-byte vectors) run through the same tiles: a
+// vector that lies inside one run of the contiguous label is one load of element alignment, one that crosses the end
+// of a run is put together element by element.
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 
 #include "eg_device.h"
 
 namespace eg {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-template <int BM_, int BN_, int WM_, int WN_, bool BF16_>
+// RAG: operands of any alignment.  WIDE: products and sums in 64 bits (v_mfma_f64_16x16x4), see launch_ragged.
+template <int BM_, int BN_, int WM_, int WN_, bool BF16_, bool RAG_ = false, bool WIDE_ = false>
 struct Cfg {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
-    static constexpr bool BF16 = BF16_;
+    static constexpr bool BF16 = BF16_, RAG = RAG_, WIDE = WIDE_;
     static constexpr int ESZ = BF16_ ? 2 : 4;             // element bytes
     static constexpr int EPC = 16 / ESZ;                  // elements per 16-byte chunk
     static constexpr int BK = 8 * EPC;                    // 8 chunks = 128 bytes per tile row
     static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN;
     static constexpr int THREADS = WAVES_M * WAVES_N * 64;
-    static constexpr int MT = WM / 32, NT = WN / 32;      // 32x32 MFMA tiles per wave
+    static constexpr int MF = WIDE_ ? 16 : 32;            // rows and columns of one MFMA
+    static constexpr int MT = WM / MF, NT = WN / MF;      // MFMA tiles per wave
     static constexpr int NVA = BM * 8 / THREADS;          // 16-byte vectors per thread per stage
     static constexpr int NVB = BN * 8 / THREADS;
     static constexpr int LDS_A = BM * 128, LDS_B = BN * 128;
@@ -98,8 +106,56 @@ __device__ __forceinline__ void transpose_store(const uint4 (&v)[NV], char *lds_
     }
 }
 
+// 16 bytes of EPC elements from an address that is a multiple of the element size only
+template <bool BF16>
+__device__ __forceinline__ uint4 load_elem_aligned(const char *p)
+{
+    uint4 v;
+    __builtin_memcpy(&v, __builtin_assume_aligned(p, BF16 ? 2 : 4), 16);
+    return v;
+}
+
+// the same number of elements, each from its own offset: at(j) is element j's offset, or -1 for a zero
+template <bool BF16, typename F>
+__device__ __forceinline__ uint4 gather_elems(const char *base, F at)
+{
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll 1
+    for (int j = 0; j < (BF16 ? 8 : 4); j++) {          // rare: code size and registers count more than its speed
+        const int64_t o = at(j);
+        uint32_t e = 0;
+        if (o >= 0) e = BF16 ? (uint32_t)((const uint16_t *)base)[o] << (16 * (j & 1)) : ((const uint32_t *)base)[o];
+#pragma unroll
+        for (int q = 0; q < 4; q++) w[q] |= q == (BF16 ? j >> 1 : j) ? e : 0u;
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// elements s .. EPC-1 of a vector, moved to the front; zeros behind them
+template <bool BF16>
+__device__ __forceinline__ uint4 drop_elems(uint4 v, int s)
+{
+    const int b = s * (BF16 ? 16 : 32);
+    if (b == 0) return v;
+    uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
+    if (b >= 64) {
+        lo = hi >> (b - 64);
+        hi = 0;
+    } else {
+        lo = lo >> b | hi << (64 - b);
+        hi >>= b;
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+
+// position of idx inside the innermost run of a group
+__device__ __forceinline__ int32_t run_pos(const DimList &g, int64_t idx)
+{
+    return g.n == 1 ? (int32_t)idx : (int32_t)((uint32_t)idx % (uint32_t)g.ext[g.n - 1]);
+}
+
 // One operand's loader state: which rows / k-rows this thread fetches and where they land in LDS.
-template <int ROWS, int NV, int THREADS, bool BF16>
+template <int ROWS, int NV, int THREADS, bool BF16, bool RAG>
 struct Loader {
     static constexpr int EPC = BF16 ? 8 : 4;
     static constexpr int CM = ROWS / EPC;            // mn-chunks per k-row (mn-contiguous mode)
@@ -107,6 +163,9 @@ struct Loader {
     int64_t row_off[NV];                             // k-contiguous mode: element offset of each fetched row
     int64_t mn_off;                                  // mn-contiguous mode: element offset of the chunk start
     bool kcontig;
+    bool cross;                                      // ragged, mn-contiguous mode: the chunk crosses into another run
+    int back;                                        // ragged, mn-contiguous mode: elements by which the chunk at the edge is read earlier
+    int32_t m_first;                                 // its first index in the group
     uint4 reg[NV];
 
     // gsel: 0 -> K strides of X (s0), 1 -> K strides of Y (s1)
@@ -114,6 +173,9 @@ struct Loader {
                                          bool kc, int tid)
     {
         kcontig = kc;
+        cross = false;
+        back = 0;
+        m_first = 0;
         base = (const char *)ptr + base_off * (BF16 ? 2 : 4);
         if (kc) {
 #pragma unroll
@@ -127,7 +189,15 @@ struct Loader {
             mn_off = 0;
         } else {
             int64_t m = first + (int64_t)(tid % CM) * EPC;
-            m = m + EPC <= extent ? m : extent - EPC;            // extent is a multiple of EPC (checked on the host)
+            if (RAG) {
+                m_first = (int32_t)(m < extent ? m : extent - 1);
+                const int32_t run = grp.ext[grp.n - 1], over = run_pos(grp, m_first) + EPC - run;
+                // The last chunk of the edge reads the EPC elements that end there and drops what lies in front of its own:
+                // element by element it took 6 us a stage where the others take 2 (1000 x 3001 x 1530: 290 us)
+                if (over > 0 && m_first + EPC > extent && run >= EPC) back = over;
+                else cross = over > 0;
+                m = m_first - back;
+            } else m = m + EPC <= extent ? m : extent - EPC;            // extent is a multiple of EPC (checked on the host)
             int64_t o0, o1;
             decode_group(grp, m, o0, o1);
             mn_off = o0;
@@ -137,13 +207,46 @@ struct Loader {
     }
 
     // Issues the global loads of the stage starting at k0.  which: 0 = X strides of K, 1 = Y strides.
-    __device__ __forceinline__ void fetch(const DimList &kgrp, int which, int64_t k0, int64_t K, int tid)
+    // (grp and extent: the row group, read only for chunks that cross the end of a run)
+    __device__ __forceinline__ void fetch(const DimList &kgrp, int which, int64_t k0, int64_t K, int tid, const DimList &grp, int64_t extent)
     {
         if (kcontig) {
             const int64_t k = k0 + (tid & 7) * EPC;
             int64_t o0, o1;
             decode_group(kgrp, k < K ? k : 0, o0, o1);
             const int64_t ko = which ? o1 : o0;
+            if (RAG) {
+                const int32_t run = kgrp.ext[kgrp.n - 1], over = run_pos(kgrp, k < K ? k : 0) + EPC - run;
+                const int early = over > 0 ? over : 0;               // as at the edge of the rows: read early, drop what is in front
+                if (k < K && (early == 0 || (k + EPC > K && run >= EPC))) {
+#pragma unroll
+                    for (int i = 0; i < NV; i++) reg[i] = load_elem_aligned<BF16>(base + (row_off[i] + ko - early) * (BF16 ? 2 : 4));
+                    if (early) {
+#pragma unroll
+                        for (int i = 0; i < NV; i++) reg[i] = drop_elems<BF16>(reg[i], early);
+                    }
+                } else if (k >= K) {
+#pragma unroll
+                    for (int i = 0; i < NV; i++) reg[i] = make_uint4(0, 0, 0, 0);
+                } else {
+#pragma unroll 1
+                    for (int i = 0; i < NV; i++) {
+                        int64_t ro = row_off[0];                     // row_off[i] without a register array indexed at run time
+#pragma unroll
+                        for (int q = 1; q < NV; q++) ro = q == i ? row_off[q] : ro;
+                        const uint4 v = gather_elems<BF16>(base, [&](int j) -> int64_t {
+                            if (k + j >= K) return -1;
+                            int64_t a0, a1;
+                            decode_group(kgrp, k + j, a0, a1);
+                            return ro + (which ? a1 : a0);
+                        });
+#pragma unroll
+                        for (int q = 0; q < NV; q++)
+                            if (q == i) reg[q] = v;
+                    }
+                }
+                return;
+            }
 #pragma unroll
             for (int i = 0; i < NV; i++) {
                 if (k < K) reg[i] = *(const uint4 *)(base + (row_off[i] + ko) * (BF16 ? 2 : 4));
@@ -151,14 +254,41 @@ struct Loader {
             }
         } else {
             const int64_t kfirst = k0 + (int64_t)(tid / CM) * NV;
+            if (RAG && cross) {
+#pragma unroll 1
+                for (int i = 0; i < NV; i++) {
+                    const int64_t k = kfirst + i;
+                    int64_t o0, o1;
+                    decode_group(kgrp, k < K ? k : 0, o0, o1);
+                    const int64_t ko = which ? o1 : o0;
+                    const uint4 v = gather_elems<BF16>(base, [&](int j) -> int64_t {       // rows past the edge repeat the last one
+                        if (k >= K) return -1;
+                        const int64_t m = m_first + j < extent ? m_first + j : extent - 1;
+                        int64_t a0, a1;
+                        decode_group(grp, m, a0, a1);
+                        return a0 + ko;
+                    });
+#pragma unroll
+                    for (int q = 0; q < NV; q++)
+                        if (q == i) reg[q] = v;
+                }
+                return;
+            }
 #pragma unroll
             for (int i = 0; i < NV; i++) {
                 const int64_t k = kfirst + i;
                 int64_t o0, o1;
                 decode_group(kgrp, k < K ? k : 0, o0, o1);
                 const int64_t ko = which ? o1 : o0;
-                if (k < K) reg[i] = *(const uint4 *)(base + (mn_off + ko) * (BF16 ? 2 : 4));
+                if (RAG) {
+                    if (k < K) reg[i] = load_elem_aligned<BF16>(base + (mn_off + ko) * (BF16 ? 2 : 4));
+                    else reg[i] = make_uint4(0, 0, 0, 0);
+                } else if (k < K) reg[i] = *(const uint4 *)(base + (mn_off + ko) * (BF16 ? 2 : 4));
                 else reg[i] = make_uint4(0, 0, 0, 0);
+            }
+            if (RAG && back) {
+#pragma unroll
+                for (int i = 0; i < NV; i++) reg[i] = drop_elems<BF16>(reg[i], back);
             }
         }
     }
@@ -217,22 +347,23 @@ __global__ __launch_bounds__(C::THREADS) void k_contract(const ContractParams p)
     }
     const int64_t m0 = (int64_t)tile_m * C::BM, n0 = (int64_t)tile_n * C::BN;
 
-    Loader<C::BM, C::NVA, C::THREADS, C::BF16> la;
-    Loader<C::BN, C::NVB, C::THREADS, C::BF16> lb;
+    Loader<C::BM, C::NVA, C::THREADS, C::BF16, C::RAG> la;
+    Loader<C::BN, C::NVB, C::THREADS, C::BF16, C::RAG> lb;
     la.init(p.x, bx, p.m, m0, p.M, p.a_kcontig != 0, tid);
     lb.init(p.y, by, p.n, n0, p.N, p.b_kcontig != 0, tid);
 
-    f32x16 acc[C::MT][C::NT];
+    constexpr int AR = C::WIDE ? 4 : 16;                     // accumulators per lane of one MFMA
+    typename std::conditional<C::WIDE, f64x4, f32x16>::type acc[C::MT][C::NT];
 #pragma unroll
     for (int i = 0; i < C::MT; i++)
 #pragma unroll
         for (int j = 0; j < C::NT; j++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
+            for (int r = 0; r < AR; r++) acc[i][j][r] = 0;
 
     const int64_t nk = (p.K + C::BK - 1) / C::BK;
-    la.fetch(p.k, 0, 0, p.K, tid);
-    lb.fetch(p.k, 1, 0, p.K, tid);
+    la.fetch(p.k, 0, 0, p.K, tid, p.m, p.M);
+    lb.fetch(p.k, 1, 0, p.K, tid, p.n, p.N);
     la.commit(smem, tid);
     lb.commit(smem + C::LDS_A, tid);
     __syncthreads();
@@ -243,9 +374,31 @@ __global__ __launch_bounds__(C::THREADS) void k_contract(const ContractParams p)
         const char *sa = smem + cur * (C::LDS_A + C::LDS_B);
         const char *sb = sa + C::LDS_A;
         if (kt + 1 < nk) {
-            la.fetch(p.k, 0, (kt + 1) * C::BK, p.K, tid);
-            lb.fetch(p.k, 1, (kt + 1) * C::BK, p.K, tid);
+            la.fetch(p.k, 0, (kt + 1) * C::BK, p.K, tid, p.m, p.M);
+            lb.fetch(p.k, 1, (kt + 1) * C::BK, p.K, tid, p.n, p.N);
         }
+        if constexpr (C::WIDE) {
+            // lane: row or column lane % 16, k = lane / 16 of four.  An MFMA takes 64 cycles, so element reads keep up
+            auto elem = [&](const char *tile, int row, int k) -> double {
+                const char *q = tile + lds_off(row, k / C::EPC) + (k % C::EPC) * C::ESZ;
+                return C::BF16 ? (double)bf16_to_f32(*(const uint16_t *)q) : (double)*(const float *)q;
+            };
+            const int64_t left = p.K - kt * C::BK;           // slots behind the last k hold zeros: whole groups of them are left out
+            const int groups = left >= C::BK ? C::BK / 4 : (int)((left + 3) / 4);
+#pragma unroll 2
+            for (int ks = 0; ks < groups; ks++) {
+                const int k = 4 * ks + (lane >> 4);
+                double a[C::MT], b[C::NT];
+#pragma unroll
+                for (int i = 0; i < C::MT; i++) a[i] = elem(sa, wm * C::WM + i * 16 + (lane & 15), k);
+#pragma unroll
+                for (int j = 0; j < C::NT; j++) b[j] = elem(sb, wn * C::WN + j * 16 + (lane & 15), k);
+#pragma unroll
+                for (int i = 0; i < C::MT; i++)
+#pragma unroll
+                    for (int j = 0; j < C::NT; j++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
+        } else
 #pragma unroll
         for (int ks = 0; ks < 4; ks++) {
             uint4 a[C::MT], b[C::NT];
@@ -275,24 +428,25 @@ __global__ __launch_bounds__(C::THREADS) void k_contract(const ContractParams p)
         __syncthreads();
     }
 
-    // ---- epilogue: lane holds column (lane % 32) and rows 8*(r/4) + 4*(lane/32) + r%4 of each 32x32 tile ----
+    // ---- epilogue: lane holds column (lane % 32) and rows 8*(r/4) + 4*(lane/32) + r%4 of each 32x32 tile; in 64 bits
+    // column (lane % 16) and rows 4*r + lane/16 of each 16x16 tile ----
     char *zb = (char *)p.out.ptr + (p.out.slab_elems ? agg * p.out.slab_elems * 4 : 0);
     const bool out_bf16 = p.out.dtype == EG_BF16;
 #pragma unroll
     for (int j = 0; j < C::NT; j++) {
-        const int64_t n = n0 + wn * C::WN + j * 32 + lrow;
+        const int64_t n = n0 + wn * C::WN + j * C::MF + (lane & (C::MF - 1));
         if (n >= p.N) continue;
         int64_t oy_unused, zn;
         decode_group(p.n, n, oy_unused, zn);
 #pragma unroll
         for (int i = 0; i < C::MT; i++) {
 #pragma unroll
-            for (int r = 0; r < 16; r++) {
-                const int64_t m = m0 + wm * C::WM + i * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
+            for (int r = 0; r < AR; r++) {
+                const int64_t m = m0 + wm * C::WM + i * C::MF + (C::WIDE ? 4 * r + (lane >> 4) : 8 * (r >> 2) + 4 * lhalf + (r & 3));
                 if (m >= p.M) continue;
                 int64_t ox_unused, zm;
                 decode_group(p.m, m, ox_unused, zm);
-                const float val = p.alpha * acc[i][j][r];
+                const float val = C::WIDE ? (float)((double)p.alpha * acc[i][j][r]) : p.alpha * (float)acc[i][j][r];
                 const int64_t off = bz + zm + zn;
                 if (out_bf16) ((uint16_t *)zb)[off] = f32_to_bf16(val);
                 else ((float *)zb)[off] = val;
@@ -344,8 +498,8 @@ __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractPa
     }
     const int64_t m0 = (int64_t)tile_m * C::BM, n0 = (int64_t)tile_n * C::BN;
 
-    Loader<C::BM, C::NVA, C::THREADS, C::BF16> la;
-    Loader<C::BN, C::NVB, C::THREADS, C::BF16> lb;
+    Loader<C::BM, C::NVA, C::THREADS, C::BF16, C::RAG> la;
+    Loader<C::BN, C::NVB, C::THREADS, C::BF16, C::RAG> lb;
     la.init(p.x, bx, p.m, m0, p.M, p.a_kcontig != 0, tid);
     lb.init(p.y, by, p.n, n0, p.N, p.b_kcontig != 0, tid);
 
@@ -355,8 +509,42 @@ __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractPa
     for (int i = 0; i < 8; i++)
 #pragma unroll
         for (int j = 0; j < 8; j++) acc[i][j] = ident;
+    // Ragged sums carry a compensation term (Kahan), as the one-output-per-lane kernel that took such shapes before did:
+    // the same terms in the same order, four more instructions per term.
+    const bool kahan = C::RAG && (OP >= 0 ? OP : p.oplus) == EG_AGG_SUM;
+    float comp[8][8];
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+#pragma unroll
+        for (int j = 0; j < 8; j++) comp[i][j] = 0.f;
 
     const int64_t nk = (p.K + C::BK - 1) / C::BK;
+
+    auto term = [&](int i, int j, float x, float y) {
+        const float v = otimes_t<OT, false>(p.otimes, x, y, p.alpha);
+        if (kahan) {
+            const float u = v - comp[i][j], s = acc[i][j] + u;
+            comp[i][j] = (s - acc[i][j]) - u;
+            acc[i][j] = s;
+        } else {
+            acc[i][j] = oplus_t<OP>(p.oplus, acc[i][j], v);
+        }
+    };
+
+    // ragged form: one k at a time, read as elements (the compensation terms take the registers of whole chunks)
+    auto one_k = [&](const char *sa, const char *sb, int k) {
+        auto elem = [&](const char *tile, int row) -> float {
+            const char *q = tile + lds_off(row, k / C::EPC) + (k % C::EPC) * C::ESZ;
+            return C::BF16 ? bf16_to_f32(*(const uint16_t *)q) : *(const float *)q;
+        };
+        float xs[8], ys[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) { xs[i] = elem(sa, ty + 16 * i); ys[i] = elem(sb, tx + 16 * i); }
+#pragma unroll
+        for (int i = 0; i < 8; i++)
+#pragma unroll
+            for (int j = 0; j < 8; j++) term(i, j, xs[i], ys[j]);
+    };
 
     // one 16-byte chunk (EPC consecutive k) of the thread's 8 rows and 8 columns; `valid` k of it count
     auto chunk = [&](const char *sa, const char *sb, int c, int valid) {
@@ -378,7 +566,7 @@ __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractPa
 #pragma unroll
             for (int i = 0; i < 8; i++)
 #pragma unroll
-                for (int j = 0; j < 8; j++) acc[i][j] = oplus_t<OP>(p.oplus, acc[i][j], otimes_t<OT, false>(p.otimes, xs[i], ys[j], p.alpha));
+                for (int j = 0; j < 8; j++) term(i, j, xs[i], ys[j]);
             __builtin_amdgcn_sched_barrier(0);       // one k at a time: unpacking all of a chunk ahead of its use costs registers
         }
     };
@@ -387,13 +575,17 @@ __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractPa
     // workgroups on the compute unit cover the loads, and the registers are needed for the 8 x 8 block.
     const char *sa = smem, *sb = smem + C::LDS_A;
     for (int64_t kt = 0; kt < nk; kt++) {
-        la.fetch(p.k, 0, kt * C::BK, p.K, tid);
-        lb.fetch(p.k, 1, kt * C::BK, p.K, tid);
+        la.fetch(p.k, 0, kt * C::BK, p.K, tid, p.m, p.M);
+        lb.fetch(p.k, 1, kt * C::BK, p.K, tid, p.n, p.N);
         la.commit(smem, tid);
         lb.commit(smem + C::LDS_A, tid);
         __syncthreads();
         const int64_t left = p.K - kt * C::BK;
-        if (left >= C::BK) {
+        if constexpr (C::RAG) {
+            const int n = left < C::BK ? (int)left : C::BK;
+#pragma unroll 1
+            for (int k = 0; k < n; k++) one_k(sa, sb, k);
+        } else if (left >= C::BK) {
 #pragma unroll 1
             for (int c = 0; c < 8; c++) chunk(sa, sb, c, C::EPC);
         } else {
@@ -488,12 +680,43 @@ bool contract_takes_dma(const ContractParams &p)
     return want_dma && contract_dma_eligible(p);
 }
 
+// Ragged operands.  Results of bf16 from bf16 operands run on the bf16 matrix instruction: their own rounding is some 1e4
+// times what fp32 accumulation adds.  Results of 32 bits were summed with a compensation term before, to a unit in the last
+// place, which an fp32 accumulator does not reach: they run on the fp64 matrix instruction, exact products and 64-bit sums.
+// 128 x 128 tiles once they fill the chip, else 64 x 64.
+// Measured against one output per lane: fp32 1121 x 319 x 646 371 -> 36 us; bf16 chain 1043 x 437 x 293 x 1156 1002 -> 60 us;
+// a classifier's step of 1000 x 3001 x 1530 x 1003 23.5 -> 0.72 ms (1000 x 3001 x 1530 to bf16 98 us, 94 TFLOP/s: a stage's
+// loads wait behind one another in 384 tiles; 3001 x 1000 x 1530 to fp32 in eight slabs 266 us, 35 of the fp64 matrix
+// instruction's 78 TFLOP/s, with two stages per tile).
+static int launch_ragged(ContractParams &p, void *stream)
+{
+    if (p.otimes != EG_MUL || p.oplus != EG_AGG_SUM) {
+        if (p.otimes < EG_MUL || p.otimes > EG_SILU_MUL) return fail(EG_ERR_BAD_OP, "contraction: scalar function %d is not binary", p.otimes);
+        if (p.in_dtype == EG_BF16) return launch_alu_ops<Cfg<128, 128, 64, 64, true, true>>(p, stream);
+        return launch_alu_ops<Cfg<128, 128, 64, 64, false, true>>(p, stream);
+    }
+    if (p.wide) {
+        if (p.in_dtype == EG_BF16) return launch_cfg<Cfg<64, 64, 32, 32, true, true, true>>(p, stream);
+        return launch_cfg<Cfg<64, 64, 32, 32, false, true, true>>(p, stream);
+    }
+    if (p.in_dtype != EG_BF16) return fail(EG_ERR_LIMIT, "contraction: ragged fp32 operands are summed in 64 bits");
+    const int64_t tiles128 = p.n_tuples * p.n_batch * ((p.M + 127) / 128) * ((p.N + 127) / 128);
+    if (tiles128 < 256) return launch_cfg<Cfg<64, 64, 32, 32, true, true>>(p, stream);
+    return launch_cfg<Cfg<128, 128, 64, 64, true, true>>(p, stream);
+}
+
 int launch_contract(ContractParams &p, void *stream)
 {
     // what the kernel assumes, re-checked here so that a wrong table can never reach the device
     if (!p.x || !p.y || !p.out.ptr) return fail(EG_ERR_NULL, "contraction: NULL operand");
     if (p.m.n < 1 || p.n.n < 1 || p.k.n < 1 || p.M < 1 || p.N < 1 || p.K < 1 || p.n_batch < 1 || p.n_tuples < 1)
         return fail(EG_ERR_LIMIT, "contraction: empty role group");
+    if (p.ragged) {
+        const bool one_a = p.a_kcontig ? p.k.s0[p.k.n - 1] == 1 : p.m.s0[p.m.n - 1] == 1;
+        const bool one_b = p.b_kcontig ? p.k.s1[p.k.n - 1] == 1 : p.n.s0[p.n.n - 1] == 1;
+        if (!one_a || !one_b) return fail(EG_ERR_LIMIT, "contraction: operand is not contiguous along its innermost label");
+        return launch_ragged(p, stream);
+    }
     const int epc = p.in_dtype == EG_BF16 ? 8 : 4;
     const bool ok_a = p.a_kcontig ? (p.k.s0[p.k.n - 1] == 1 && p.k.ext[p.k.n - 1] % epc == 0)
                                   : (p.m.s0[p.m.n - 1] == 1 && p.m.ext[p.m.n - 1] % epc == 0);

@@ -728,7 +728,7 @@ static int launch_layout(ContractParams &p, void *stream)
 
 bool contract_dma_eligible(const ContractParams &p)
 {
-    if (p.in_dtype != EG_BF16 && p.in_dtype != EG_F32) return false;
+    if (p.ragged || (p.in_dtype != EG_BF16 && p.in_dtype != EG_F32)) return false;
     const bool f32 = p.in_dtype == EG_F32;
     const int64_t es = f32 ? 4 : 2, epc = 16 / es, bk = 128 / es;
     if (p.m.n < 1 || p.n.n < 1 || p.k.n < 1) return false;
