@@ -323,14 +323,25 @@ __global__ __launch_bounds__(kThreads) void k_reduce_row(const ReduceParams p)
     }
 }
 
+// 8 bf16 as they lie in memory -> fp32
+__device__ __forceinline__ void unpack8(const uint4 r, float (&v)[8])
+{
+    v[0] = __uint_as_float(r.x << 16); v[1] = __uint_as_float(r.x & 0xffff0000u);
+    v[2] = __uint_as_float(r.y << 16); v[3] = __uint_as_float(r.y & 0xffff0000u);
+    v[4] = __uint_as_float(r.z << 16); v[5] = __uint_as_float(r.z & 0xffff0000u);
+    v[6] = __uint_as_float(r.w << 16); v[7] = __uint_as_float(r.w & 0xffff0000u);
+}
+
 // Short rows: an (output, piece) has at most LANES vectors, one per lane, and a group of LANES lanes takes R
 // consecutive ones, loading all R vectors before it reduces any.  A wave that held a single kilobyte in flight and
 // then walked through its cross-lane reduction left the memory system idle most of the time (0.6 TB/s on rows of 128
 // elements, 2.4 on rows of 512; with this 4-5 TB/s).
 // RUN: the R outputs lie behind one another in the innermost output dimension (unsplit, its extent a multiple of R), so
 // a lane decodes its offsets once and steps along that dimension's strides.  The decode (a division per dimension and
-// output) was most of the kernel: scores of one query against 8 x 32 x 2048 keys of 128 (134 MB) took 63 us, now 39.5.
-template <int LANES, int OP, int OPLUS, int R, bool RUN>
+// output) was most of the kernel: scores of one query against 8 x 32 x 2048 keys of 128 (134 MB) took 63 us, 39.5 decoded once, 29.4 with typed loads.
+// BF: the operands are bf16 in vectors, known at compile time: with the type read at run time every load is a branch
+// that ends in its conversion, so each waits for the one before it.
+template <int LANES, int OP, int OPLUS, int R, bool RUN, bool BF>
 __global__ __launch_bounds__(kThreads) void k_reduce_short(const ReduceParams p)
 {
     constexpr int PER_WG = kThreads / LANES, VEC = 8;
@@ -373,9 +384,23 @@ __global__ __launch_bounds__(kThreads) void k_reduce_short(const ReduceParams p)
         for (int r = 0; r < R; r++) {
             act[r] = live; ok[r] = on; piece[r] = 0;
             oz[r] = o0 + r * p.zdims.sz[zl];
-            if (on) load8(p.x, p.dtx, ox + r * p.zdims.sx[zl], x[r]);
+            if (!BF && on) load8(p.x, p.dtx, ox + r * p.zdims.sx[zl], x[r]);
         }
-        if (p.binary && on) {
+        if constexpr (BF) {
+            if (on) {
+                uint4 xr[R], yr[R];
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    xr[r] = *(const uint4 *)((const uint16_t *)p.x + ox + r * p.zdims.sx[zl]);
+                    if (OP == EG_MUL) yr[r] = *(const uint4 *)((const uint16_t *)p.y + oy + r * p.zdims.sy[zl]);
+                }
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    unpack8(xr[r], x[r]);
+                    if (OP == EG_MUL) unpack8(yr[r], y[r]);
+                }
+            }
+        } else if (p.binary && on) {
 #pragma unroll
             for (int r = 0; r < R; r++) {
                 const int64_t by = oy + r * p.zdims.sy[zl];
@@ -457,7 +482,9 @@ __global__ __launch_bounds__(kThreads) void k_reduce_short(const ReduceParams p)
 // tens of thousands of same-signed terms.
 constexpr int kColStrip = 32, kColGroups = kThreads / kColStrip;
 
-template <int OP, int OPLUS>
+// BF: bf16 operands, known at compile time as in k_reduce_short; VX, VY: X, Y is read in vectors (else as one value).
+// P x V of one query, 8 x 32 x 2048 values of 128 (134 MB), took 53 us with 32 loads one after the other, 32 now.
+template <int OP, int OPLUS, bool BF = false, bool VX = false, bool VY = false>
 __global__ __launch_bounds__(kThreads) void k_reduce_col(const ReduceParams p)
 {
     constexpr int VEC = 8, U = 4;
@@ -498,6 +525,8 @@ __global__ __launch_bounds__(kThreads) void k_reduce_col(const ReduceParams p)
     for (int i = 0; i < VEC; i++) { acc[i] = oplus_identity(OPLUS >= 0 ? OPLUS : p.oplus); comp[i] = 0.f; }
     for (uint32_t j0 = lo; active && j0 < hi; j0 += U) {
         float x[U][VEC], y[U][VEC];
+        uint4 xr[U], yr[U];                                          // BF: all loads of the step before the first conversion
+        uint16_t xs[U], ys[U];
 #pragma unroll
         for (int u = 0; u < U; u++) {
             const uint32_t j = j0 + u < hi ? j0 + u : lo;           // a valid position; its values are not used
@@ -509,6 +538,15 @@ __global__ __launch_bounds__(kThreads) void k_reduce_col(const ReduceParams p)
                 const int64_t k2 = q - q2 * ext;
                 q = q2;
                 bx += k2 * p.rdims.sx[i]; by += k2 * p.rdims.sy[i];
+            }
+            if constexpr (BF) {
+                if (VX) xr[u] = *(const uint4 *)((const uint16_t *)p.x + bx);
+                else xs[u] = ((const uint16_t *)p.x)[bx];
+                if (OP == EG_MUL) {
+                    if (VY) yr[u] = *(const uint4 *)((const uint16_t *)p.y + by);
+                    else ys[u] = ((const uint16_t *)p.y)[by];
+                }
+                continue;
             }
             if (xvec) load8(p.x, p.dtx, bx, x[u]);
             else { const float sv = load_elem(p.x, p.dtx, bx);
@@ -522,6 +560,15 @@ __global__ __launch_bounds__(kThreads) void k_reduce_col(const ReduceParams p)
 #pragma unroll
         for (int u = 0; u < U; u++) {
             if (j0 + u >= hi) continue;
+            if constexpr (BF) {
+                if (VX) unpack8(xr[u], x[u]);
+                if (OP == EG_MUL && VY) unpack8(yr[u], y[u]);
+#pragma unroll
+                for (int i = 0; i < VEC; i++) {
+                    if (!VX) x[u][i] = bf16_to_f32(xs[u]);
+                    if (OP == EG_MUL && !VY) y[u][i] = bf16_to_f32(ys[u]);
+                }
+            }
 #pragma unroll
             for (int i = 0; i < VEC; i++) {
                 const float v = otimes_t<OP, false>(p.otimes, x[u][i], p.binary ? y[u][i] : 0.f, p.alpha);
@@ -765,20 +812,23 @@ int launch_map(const MapParams &p, void *stream)
     return check_launch("k_map");
 }
 
-template <int LANES, int R, bool RUN>
+template <int LANES, int R, bool RUN, bool BF>
 static void launch_reduce_short_ops(const ReduceParams &p, dim3 grid, hipStream_t st)
 {
-    if (p.otimes == EG_IDENT && p.oplus == EG_AGG_MAX) EG_LAUNCH((k_reduce_short<LANES, EG_IDENT, EG_AGG_MAX, R, RUN>), grid, dim3(kThreads), 0, st, p);
-    else if (p.otimes == EG_IDENT && p.oplus == EG_AGG_SUM) EG_LAUNCH((k_reduce_short<LANES, EG_IDENT, EG_AGG_SUM, R, RUN>), grid, dim3(kThreads), 0, st, p);
-    else if (p.otimes == EG_MUL && p.oplus == EG_AGG_SUM) EG_LAUNCH((k_reduce_short<LANES, EG_MUL, EG_AGG_SUM, R, RUN>), grid, dim3(kThreads), 0, st, p);
-    else EG_LAUNCH((k_reduce_short<LANES, -1, -1, R, RUN>), grid, dim3(kThreads), 0, st, p);
+    if (p.otimes == EG_IDENT && p.oplus == EG_AGG_MAX) EG_LAUNCH((k_reduce_short<LANES, EG_IDENT, EG_AGG_MAX, R, RUN, BF>), grid, dim3(kThreads), 0, st, p);
+    else if (p.otimes == EG_IDENT && p.oplus == EG_AGG_SUM) EG_LAUNCH((k_reduce_short<LANES, EG_IDENT, EG_AGG_SUM, R, RUN, BF>), grid, dim3(kThreads), 0, st, p);
+    else if (p.otimes == EG_MUL && p.oplus == EG_AGG_SUM) EG_LAUNCH((k_reduce_short<LANES, EG_MUL, EG_AGG_SUM, R, RUN, BF>), grid, dim3(kThreads), 0, st, p);
+    else EG_LAUNCH((k_reduce_short<LANES, -1, -1, R, RUN, false>), grid, dim3(kThreads), 0, st, p);
 }
 
 template <int LANES, int R>
 static void launch_reduce_short(const ReduceParams &p, dim3 grid, hipStream_t st)
 {
-    if (p.split == 1 && p.zdims.n >= 1 && p.zdims.ext[p.zdims.n - 1] % R == 0) launch_reduce_short_ops<LANES, R, true>(p, grid, st);
-    else launch_reduce_short_ops<LANES, R, false>(p, grid, st);
+    const bool run = p.split == 1 && p.zdims.n >= 1 && p.zdims.ext[p.zdims.n - 1] % R == 0;
+    const bool bf = p.dtx == EG_BF16 && (!p.binary || (p.dty == EG_BF16 && p.rdims.sy[p.rdims.n - 1] == 1));
+    if (run && bf) launch_reduce_short_ops<LANES, R, true, true>(p, grid, st);
+    else if (run) launch_reduce_short_ops<LANES, R, true, false>(p, grid, st);
+    else launch_reduce_short_ops<LANES, R, false, false>(p, grid, st);
 }
 
 template <int LANES, int VEC, int U>
@@ -805,7 +855,13 @@ int launch_reduce_row(const ReduceParams &p, void *stream)
         dim3 grid;
         int rc = tuple_grid((p.outs_per_block / 8 + kColStrip - 1) / kColStrip * p.split, 1, p.n_tuples, grid);
         if (rc) return rc;
-        if (p.otimes == EG_IDENT && p.oplus == EG_AGG_SUM) EG_LAUNCH((k_reduce_col<EG_IDENT, EG_AGG_SUM>), grid, dim3(kThreads), 0, st, p);
+        const bool bf = p.dtx == EG_BF16 && (!p.binary || p.dty == EG_BF16), vx = p.zdims.sx[zd] == 1, vy = p.binary && p.zdims.sy[zd] == 1;
+        const bool sum = p.oplus == EG_AGG_SUM, mul = p.otimes == EG_MUL && sum;
+        if (bf && vx && p.otimes == EG_IDENT && sum) EG_LAUNCH((k_reduce_col<EG_IDENT, EG_AGG_SUM, true, true, false>), grid, dim3(kThreads), 0, st, p);
+        else if (bf && vx && vy && mul) EG_LAUNCH((k_reduce_col<EG_MUL, EG_AGG_SUM, true, true, true>), grid, dim3(kThreads), 0, st, p);
+        else if (bf && vx && mul) EG_LAUNCH((k_reduce_col<EG_MUL, EG_AGG_SUM, true, true, false>), grid, dim3(kThreads), 0, st, p);
+        else if (bf && vy && mul) EG_LAUNCH((k_reduce_col<EG_MUL, EG_AGG_SUM, true, false, true>), grid, dim3(kThreads), 0, st, p);
+        else if (p.otimes == EG_IDENT && p.oplus == EG_AGG_SUM) EG_LAUNCH((k_reduce_col<EG_IDENT, EG_AGG_SUM>), grid, dim3(kThreads), 0, st, p);
         else if (p.otimes == EG_IDENT && p.oplus == EG_AGG_MAX) EG_LAUNCH((k_reduce_col<EG_IDENT, EG_AGG_MAX>), grid, dim3(kThreads), 0, st, p);
         else if (p.otimes == EG_MUL && p.oplus == EG_AGG_SUM) EG_LAUNCH((k_reduce_col<EG_MUL, EG_AGG_SUM>), grid, dim3(kThreads), 0, st, p);
         else EG_LAUNCH((k_reduce_col<-1, -1>), grid, dim3(kThreads), 0, st, p);
