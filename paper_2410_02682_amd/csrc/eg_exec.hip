@@ -382,7 +382,8 @@ static int route(const Vertex &v, const Operand &X, const Operand *Y, const std:
     // The same with operands that are no whole 16-byte vectors.  Fewer outputs than a tile, and reductions shorter than one
     // matrix step, stay on the reductions and the one-output-per-lane kernel below, which cut a long reduction into pieces.
     // Other scalar functions need 64 tiles of 128 x 128: a tile is some 0.9 us of vector work per contracted element whatever
-    // the number of tiles, and one output per lane is level with 30 of them (1059 x 273 x 184, 18 tiles: 975 us against 587).
+    // the number of tiles, and one output per lane is level with 30 of them (four products each: 1059 x 273 x 184,
+    // 18 tiles, 975 us against 587; 1964 x 145 x 1355, 176 tiles, 499 us against 5920).
     auto suits_tiles = [&](const ContractParams &c) {
         if (c.K < 16) return false;
         if (v.otimes == EG_MUL && v.oplus == EG_AGG_SUM) return c.M * c.N * c.n_batch * n_tuples >= 4096;
