@@ -7,6 +7,22 @@
 
 namespace eg {
 
+// A kernel's parameters are up to 2.7 KB and read by scalar loads where they are used, one round trip to memory after another:
+// 5000 to 6000 cycles at the head of a contraction before its first operand is asked for.  This reads a word of every 64-byte
+// line of them at once, so that the scalar cache has them when they are wanted: 1900 cycles, and a contraction of 2048 x 256 x
+// 2048 goes from 13.6 to 12.0 us.  The reads cost each wave some
+// 20 scalar instructions: not for the element-by-element softmax (24.5 to 26.1 us on 1000 rows of 1003), and aggregations, whose
+// parameters are 288 bytes, gain nothing.
+template <int BYTES>
+__device__ __forceinline__ void fetch_params()
+{
+    const __attribute__((address_space(4))) uint32_t *q = (const __attribute__((address_space(4))) uint32_t *)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t v = 0;
+#pragma unroll
+    for (int i = 0; i < BYTES; i += 64) v ^= q[i / 4];
+    asm volatile("" ::"s"(v));
+}
+
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
 // fp32 -> bf16, round to nearest, ties to even (the hardware conversion of gfx950).

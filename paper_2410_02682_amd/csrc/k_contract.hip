@@ -313,6 +313,7 @@ struct Loader {
 template <typename C>
 __global__ __launch_bounds__(C::THREADS, C::TOTALS ? 4 : 1) void k_contract(const ContractParams p)
 {
+    fetch_params<sizeof(ContractParams)>();
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
@@ -496,6 +497,7 @@ __global__ __launch_bounds__(C::THREADS, C::TOTALS ? 4 : 1) void k_contract(cons
 template <typename C, int OT, int OP>
 __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractParams p)
 {
+    fetch_params<sizeof(ContractParams)>();
     static_assert(C::BM == 128 && C::BN == 128 && C::THREADS == 256, "16 x 16 threads of 8 x 8 outputs");
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;

@@ -234,6 +234,7 @@ constexpr int lds_bytes(int TM, int TN, int KB, int NW, int NS)
 template <int TM, int TN, int KB, int NS, int NW, bool A_KC, bool B_KC, int REM, bool F32>
 __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, NW, NS) <= 160 * 1024 ? 2 : 1) void k_contract_dma(const ContractParams p)
 {
+    fetch_params<sizeof(ContractParams)>();
     constexpr int ES = Elem<F32>::ES, EPC = Elem<F32>::EPC, BK = KB / ES;
     constexpr int KS = KB / 32;                       // k-steps per stage (32 bytes of k each)
     constexpr int WN = NW / 2;                        // waves side by side
@@ -909,6 +910,7 @@ __device__ __forceinline__ int64_t agg_tiles_offset(const DimList &g, int64_t id
 template <int N>
 __global__ __launch_bounds__(256) void k_aggregate_patches(const AggTilesParams p)
 {
+    fetch_params<sizeof(AggTilesParams)>();
     __shared__ int64_t zr[128], zc[128];               // Z offsets of the patch's rows and columns
     __shared__ __attribute__((aligned(16))) float rows[32 * (128 + 4)];    // 32 rows of the patch on their way from register order to row order
     const int tid = threadIdx.x;

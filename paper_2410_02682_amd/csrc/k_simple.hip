@@ -29,6 +29,7 @@ __device__ __forceinline__ char *out_base(const OutSpec &o, int64_t agg)
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kThreads) void k_generic(const GenericParams p)
 {
+    fetch_params<sizeof(GenericParams)>();
     const int64_t gid = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (gid >= p.n_tuples * p.outs_per_block) return;
     const int64_t t = gid / p.outs_per_block, e = gid - t * p.outs_per_block;
@@ -93,6 +94,7 @@ __device__ __forceinline__ uint32_t pos_of_block() { return blockIdx.z * gridDim
 template <int VEC, int OP, bool FAST>
 __global__ __launch_bounds__(kThreads) void k_map(const MapParams p)
 {
+    fetch_params<sizeof(MapParams)>();
     const int64_t t = tuple_of_block();
     const uint32_t pos = pos_of_block();
     int64_t ox, oy, oz, agg;
@@ -154,6 +156,7 @@ constexpr int kTrTile = 64;
 template <int OP, bool FAST>
 __global__ __launch_bounds__(kThreads) void k_map_tr(const MapParams p)
 {
+    fetch_params<sizeof(MapParams)>();
     __shared__ float tile[kTrTile][kTrTile + 1];
     const int64_t t = tuple_of_block();
     uint32_t pos = pos_of_block();
@@ -233,6 +236,7 @@ __device__ __forceinline__ float wave_reduce(int oplus, float v)
 template <int LANES, int VEC, int OP, int OPLUS, int U>
 __global__ __launch_bounds__(kThreads) void k_reduce_row(const ReduceParams p)
 {
+    fetch_params<sizeof(ReduceParams)>();
     constexpr int PER_WG = kThreads / LANES;
     __shared__ float red[kThreads / 64];
     const int sub = threadIdx.x / LANES, lane = threadIdx.x % LANES;
@@ -344,6 +348,7 @@ __device__ __forceinline__ void unpack8(const uint4 r, float (&v)[8])
 template <int LANES, int OP, int OPLUS, int R, bool RUN, bool BF>
 __global__ __launch_bounds__(kThreads) void k_reduce_short(const ReduceParams p)
 {
+    fetch_params<sizeof(ReduceParams)>();
     constexpr int PER_WG = kThreads / LANES, VEC = 8;
     const int sub = threadIdx.x / LANES, lane = threadIdx.x % LANES;
     const int64_t t = tuple_of_block();
@@ -487,6 +492,7 @@ constexpr int kColStrip = 32, kColGroups = kThreads / kColStrip;
 template <int OP, int OPLUS, bool BF = false, bool VX = false, bool VY = false>
 __global__ __launch_bounds__(kThreads) void k_reduce_col(const ReduceParams p)
 {
+    fetch_params<sizeof(ReduceParams)>();
     constexpr int VEC = 8, U = 4;
     __shared__ float part[kColGroups][kColStrip][VEC + 1];
     const int64_t t = tuple_of_block();
@@ -1074,6 +1080,7 @@ __device__ __forceinline__ void static_for(F &&f)
 template <int VPL, int MODE, bool TAIL>
 __global__ __launch_bounds__(kThreads) void k_softmax_rows(const SoftmaxParams p)
 {
+    fetch_params<sizeof(SoftmaxParams)>();
     static_assert(!TAIL || MODE == 2, "tails come with run-time dtypes");
     const int dt_t = MODE == 0 ? EG_BF16 : MODE == 1 ? EG_F32 : p.dt_t;
     const int dt_e = MODE == 0 ? EG_BF16 : MODE == 1 ? EG_F32 : p.dt_e;
@@ -1228,6 +1235,7 @@ __global__ __launch_bounds__(kThreads) void k_softmax_rows(const SoftmaxParams p
 template <int VPL, int R, int ADD>
 __global__ __launch_bounds__(kThreads) void k_softmax_rows_bf16(const SoftmaxParams p)
 {
+    fetch_params<sizeof(SoftmaxParams)>();
     typedef uint32_t raw4 __attribute__((ext_vector_type(4)));
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t t = tuple_of_block();
