@@ -252,8 +252,12 @@ int tr_set_fused_aggregation(eg_graph *g, int enable);
  * 4.3's two stages, unchanged).  enable != 0 (the default): when the vertex's blocks are whole output tiles of that kernel,
  * a partial slab holds the tiles one after the other, each in the order the kernel's accumulators lie in registers, and
  * the aggregation kernel that follows undoes the order; same workspace size, same sums in the same order, results equal
- * bit for bit.  enable = 0: every slab is the dense row-major tensor (what tr_aggregate takes).  For comparisons and
- * tests.  Takes effect at the next tr_execute. */
+ * bit for bit.  And where that is estimated to be faster, the kernel walks over the blocks that share an output block and
+ * adds their sums itself, in the same order, each scaled and rounded as its slab would hold it: nothing is written in
+ * between and no aggregation launch follows (the results are the same bit for bit, or, where the kernel splits a tile's
+ * reduction over two groups of waves, sums of the same terms in another order).  enable = 0: every slab is the dense
+ * row-major tensor (what tr_aggregate takes) and is aggregated.  For comparisons and tests.  Takes effect at the next
+ * tr_execute. */
 int tr_set_tiled_partials(eg_graph *g, int enable);
 
 /* Another alternative for comparison, off by default.  Section 3 writes attention as a contraction Q x K^T over the head

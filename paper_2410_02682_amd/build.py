@@ -10,8 +10,9 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libeindecomp.so")
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ["eg_graph.cpp", "eg_planner.cpp", "eg_exec.hip", "k_simple.hip", "k_contract.hip", "k_contract_dma.hip", "k_attention.hip", "k_ceilings.hip"]
-HEADERS = [os.path.join(CSRC, "eg_internal.h"), os.path.join(CSRC, "eg_device.h"), os.path.join(INCLUDE, "eindecomp.h")]
+SOURCES = ["eg_graph.cpp", "eg_planner.cpp", "eg_exec.hip", "k_simple.hip", "k_contract.hip", "k_contract_dma.hip", "k_contract_dma_256.hip",
+           "k_contract_dma_128.hip", "k_contract_dma_totals.hip", "k_attention.hip", "k_ceilings.hip"]
+HEADERS = [os.path.join(CSRC, "eg_internal.h"), os.path.join(CSRC, "eg_device.h"), os.path.join(CSRC, "k_contract_dma.h"), os.path.join(INCLUDE, "eindecomp.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE, "-I" + CSRC,
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
          "-Wno-unknown-warning-option", "-Wno-unused-command-line-argument"]
@@ -40,7 +41,7 @@ def _compile(src, force):
 
 def build(force: bool = False) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=4) as ex:
+    with ThreadPoolExecutor(max_workers=6) as ex:
         objs = list(ex.map(lambda s: _compile(s, force), SOURCES))
     if force or _stale(LIB, objs):
         cmd = ["hipcc", "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs

@@ -170,6 +170,37 @@ __device__ __forceinline__ int64_t tuple_group(const TupleSpace &ts, int64_t t)
     return g;
 }
 
+// Output block index -> offsets of the block in Z and of the first blocks along the aggregated labels in X and Y ...
+__device__ __forceinline__ void group_offsets(const TupleSpace &ts, int64_t g, int64_t &ox, int64_t &oy, int64_t &oz)
+{
+    ox = oy = oz = 0;
+    uint32_t rem = (uint32_t)g;
+    for (int l = ts.n - 1; l >= 0; l--) {
+        if (ts.grp_w[l] == 0) continue;
+        uint32_t dd = (uint32_t)ts.d[l];
+        uint32_t q = rem / dd, k = rem - q * dd;
+        rem = q;
+        ox += (int64_t)k * ts.step_x[l];
+        oy += (int64_t)k * ts.step_y[l];
+        oz += (int64_t)k * ts.step_z[l];
+    }
+}
+
+// ... and aggIdx -> offsets in X and Y of that block from the first.
+__device__ __forceinline__ void agg_offsets(const TupleSpace &ts, uint32_t agg, int64_t &ox, int64_t &oy)
+{
+    ox = oy = 0;
+    uint32_t rem = agg;
+    for (int l = ts.n - 1; l >= 0; l--) {
+        if (ts.agg_w[l] == 0) continue;
+        uint32_t dd = (uint32_t)ts.d[l];
+        uint32_t q = rem / dd, k = rem - q * dd;
+        rem = q;
+        ox += (int64_t)k * ts.step_x[l];
+        oy += (int64_t)k * ts.step_y[l];
+    }
+}
+
 // ... and back: output block index -> Z offset of the block.
 __device__ __forceinline__ int64_t group_offset_z(const TupleSpace &ts, int64_t g)
 {

@@ -1611,6 +1611,23 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
             s.r.cp.force_tile_n = g->contract_tile_n;
             s.r.cp.force_waves = g->contract_waves;
         }
+        // Blocks along aggregated labels whose sums the kernel can total itself, where that is faster: no slabs, no aggregation.  (The
+        // slabs stay in the workspace's layout, which does not know the strides and addresses that relations are bound with.)
+        if (s.agg && !refined && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && contract_takes_dma(s.r.cp) &&
+            contract_totals_pay(s.r.cp, s.slabs, (int)dtype_size(v.dtype))) {
+            const OutSpec direct{s.dst, 0, (int32_t)v.dtype};
+            Routed rt;
+            if (route(*routed, X, &Y, Z.stride, direct, rt, 1) == EG_OK && rt.kind == EG_KERNEL_CONTRACT_MFMA && !rt.ragged) {
+                rt.cp.n_totals = (int32_t)s.slabs;
+                rt.cp.n_tuples /= s.slabs;
+                rt.cp.force_kernel = s.r.cp.force_kernel;
+                rt.cp.force_waves = s.r.cp.force_waves;
+                if (contract_takes_dma(rt.cp)) {
+                    s.r = rt;
+                    s.agg = false;
+                }
+            }
+        }
         // Partial slabs of the direct-to-LDS contraction kernel in tile order when its tiles are whole: the slab has the same
         // size, only the order of its elements is a matter between that kernel and the aggregation that follows it.  The join
         // kernel saves some 5 us per tile (no staging through LDS), the aggregation of tile-ordered slabs runs at 0.70 of the
@@ -1618,8 +1635,8 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
         // count (up to 4096; config 6's product with 12800 per tile lost 0.5 % per step with it).
         if (s.agg && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA && s.r.cp.K <= 4096 && contract_takes_dma(s.r.cp)) {
             const Vertex &vu = *routed;
-            int tm = 0, tn = 0, nw = 0;
-            contract_dma_variant(s.r.cp, tm, tn, nw);
+            int tm = 0, tn = 0, nw = 0, ns = 0;
+            contract_dma_variant(s.r.cp, tm, tn, nw, ns);
             const ContractParams &cp = s.r.cp;
             if (tm > 0 && cp.M % tm == 0 && cp.N % tn == 0 && vu.plan.n_tuples % s.slabs == 0 && v.n_in == 2 &&
                 tiles_params(vu, X, Y, Z.stride, s.r, s.tp)) {

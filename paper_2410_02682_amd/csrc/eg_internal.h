@@ -75,6 +75,7 @@ struct ContractParams {
     int32_t force_waves;          // 0: the launcher chooses; 4 / 8: waves per workgroup of the 256 x 256 direct-to-LDS kernel
     int32_t tile_order;           // 1: partial slabs are written tile after tile in the accumulators' order (see AggTilesParams)
     int32_t k_stages;             // filled by the launcher of the direct-to-LDS kernel: stages per output tile
+    int32_t n_totals;             // > 1: the kernel walks over this many blocks along the aggregated labels and keeps the totals of their sums; n_tuples counts output blocks then
     int32_t ragged;               // 1: extents, strides or addresses are no whole 16-byte vectors; the register-staged kernels' ragged form
     int32_t wide;                 // ragged products on the fp64 instruction: all but those of bf16 operands to a bf16 vertex
     int32_t k_align;              // filled by that launcher: 0: a tile's stages start at its block's first k; 1 / 2: on the 128-byte line of X / Y below it
@@ -251,7 +252,8 @@ int launch_softmax_rows(SoftmaxParams &p, void *stream);
 int launch_attention(AttnParams &p, void *stream);
 int launch_aggregate_tiles(AggTilesParams &p, void *stream);
 bool contract_takes_dma(const ContractParams &p);                              // launch_contract will hand p to the direct-to-LDS kernel
-void contract_dma_variant(const ContractParams &p, int &tm, int &tn, int &nw);   // ... which will run this tile shape and wave count
+void contract_dma_variant(const ContractParams &p, int &tm, int &tn, int &nw, int &ns);   // ... which will run this tile shape, wave count and number of stages
+bool contract_totals_pay(const ContractParams &p, int64_t n_agg, int out_bytes);   // ... and faster with totals kept in the kernel than through partial slabs
 size_t attention_mask_class_bytes(int64_t S, int64_t T);
 
 // ------------------------------------------------------------------------------------------------

@@ -767,6 +767,7 @@ int launch_contract(ContractParams &p, void *stream)
     }
     const int64_t tiles128 = p.n_tuples * p.n_batch * ((p.M + 127) / 128) * ((p.N + 127) / 128);
     if (contract_takes_dma(p)) return launch_contract_dma(p, stream);
+    if (p.n_totals > 1) return fail(EG_ERR_LIMIT, "contraction: totals of blocks are kept by the direct-to-LDS kernel only");
     if (tiles128 <= 64) {
         if (p.in_dtype == EG_BF16) return launch_cfg<Cfg<64, 64, 32, 32, true>>(p, stream);
         return launch_cfg<Cfg<64, 64, 32, 32, false>>(p, stream);
