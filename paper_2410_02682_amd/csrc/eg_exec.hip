@@ -274,6 +274,7 @@ struct Routed {
     int kind = EG_KERNEL_NONE;
     bool ragged = false;           // contraction: on the ragged form of the kernels
     bool swapped = false;          // contraction: X and Y changed places (see route)
+    int row_pieces = 0;            // contraction: > 0: on the few-row kernel, cut into so many pieces
     ContractParams cp;
     MapParams mp;
     ReduceParams rp;
@@ -979,6 +980,16 @@ static Vertex whole_vertex(const Vertex &v)
     return m;
 }
 
+// the vertex in one piece: cuts of other labels are views only, and a kernel that cuts the contracted labels itself does not need theirs
+static Vertex single_vertex(const Vertex &v)
+{
+    Vertex m = unplanned_copy(v);
+    std::fill(m.d.begin(), m.d.end(), 1);
+    m.plan.n_tuples = m.plan.n_agg = m.plan.n_groups = 1;
+    m.plan.valid = true;
+    return m;
+}
+
 // An under-filled contraction with a long reduction (a matrix times a few vectors, a small product of long rows):
 // the executor cuts one contracted label further than the vertex's own vector says, as many ways as it takes to
 // give the chip's compute units a tile each.  The pieces are ordinary join tuples that write partial slabs, which
@@ -1157,7 +1168,7 @@ static int launch_routed(Routed &r, void *stream)
 {
     switch (r.kind) {
     case EG_KERNEL_CONTRACT_MFMA:
-    case EG_KERNEL_CONTRACT_ALU: return launch_contract(r.cp, stream);
+    case EG_KERNEL_CONTRACT_ALU: return r.row_pieces ? launch_contract_rows(r.cp, r.row_pieces, stream) : launch_contract(r.cp, stream);
     case EG_KERNEL_MAP: return launch_map(r.mp, stream);
     case EG_KERNEL_REDUCE_ROW: return launch_reduce_row(r.rp, stream);
     case EG_KERNEL_GENERIC: return launch_generic(r.gp, stream);
@@ -1610,6 +1621,33 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
             s.r.cp.force_tile_m = g->contract_tile_m;
             s.r.cp.force_tile_n = g->contract_tile_n;
             s.r.cp.force_waves = g->contract_waves;
+        }
+        // Few rows times a large matrix: a kernel that streams the matrix, cut along the contracted label into no more pieces than the
+        // vertex has slabs in the workspace.
+        if (!merged && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && s.r.cp.M <= 16 && !s.r.cp.force_kernel && !s.r.cp.force_tile_m && !s.r.cp.force_waves) {
+            const Vertex v1 = single_vertex(v);
+            Routed rt;
+            const OutSpec direct{s.dst, 0, (int32_t)v.dtype};
+            if (route(v1, X, &Y, Z.stride, direct, rt, 1) == EG_OK && rt.kind == EG_KERNEL_CONTRACT_MFMA && !rt.ragged && contract_rows_suits(rt.cp)) {
+                const int64_t room = L.partial_off[i] >= 0 ? v.plan.n_agg * L.split[i] : 1;
+                const int pieces = contract_rows_pieces(rt.cp, room);
+                const OutSpec slabs{pieces > 1 ? ws + L.partial_off[i] : nullptr, slab_stride_of(numel(v.bound), pieces), EG_F32};
+                bool ok = true;
+                if (pieces > 1) {
+                    rt = Routed();
+                    ok = route(v1, X, &Y, dense_strides(v.bound), slabs, rt, 1) == EG_OK && rt.kind == EG_KERNEL_CONTRACT_MFMA && !rt.ragged && contract_rows_suits(rt.cp);
+                }
+                if (ok) {
+                    rt.row_pieces = pieces;
+                    s.r = rt;
+                    s.slabs = pieces;
+                    s.agg = pieces > 1;
+                    s.partials = slabs.ptr;
+                    s.stride = slabs.slab_elems;
+                    steps.push_back(std::move(s));
+                    continue;
+                }
+            }
         }
         // Blocks along aggregated labels whose sums the kernel can total itself, where that is faster: no slabs, no aggregation.  (The
         // slabs stay in the workspace's layout, which does not know the strides and addresses that relations are bound with.)

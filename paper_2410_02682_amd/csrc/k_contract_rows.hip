@@ -1,0 +1,205 @@
+// Block contraction of a few rows with a large matrix (a token's activations times a weight matrix): X has at most 16 rows, each
+// contiguous along the one contracted label; Y is whole 16-byte vectors along its columns or along the contracted label.
+//
+// Bound by the way of Y from memory.  The 128 x 128 tiles spend their LDS, barriers and stages on rows that are not there; here
+// every wave streams its own part of Y into registers, two iterations of 4 or 8 KiB in flight (four were slower: waves have four
+// to sixteen iterations, and branches around the loads make the compiler wait for all of them), and feeds it to 16x16x32 MFMAs
+// whose other operand is X, padded to 16 rows by loads outside its descriptor.  No LDS before the end, where the eight waves of a
+// workgroup, which split its part of the contracted label, add their sums in ascending order.  us with Y from memory, aggregation
+// of the pieces included, tiles before: 8 x 4096 x 4096 24.3 -> 14.1 (33.5 MB), 8 x 4096 x 11008 28.4 -> 23.1, 8 x 11008 x 4096
+// 29.9 -> 22.0, 8 x 4096 x 4096 with Y along k 19.3 -> 12.8.
+//   Y contiguous along its columns: a lane takes VC neighbouring columns of eight consecutive k and turns them around in
+//       registers (v_perm), which gives VC fragments; fragment f of lane c stands for column VC * c + f of the wave's 16 * VC.
+//   Y contiguous along k: a lane's 16 bytes are a fragment already; a wave takes 16 columns and 256 k per iteration.
+// A launch is cut along the contracted label into as many pieces as the vertex has partial slabs, where its columns alone do not
+// give every compute unit a workgroup.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "eg_device.h"
+
+namespace eg {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+namespace rows {
+
+constexpr int kWaves = 8;
+
+__device__ __forceinline__ void decode(const DimList &g, int64_t idx, int64_t &o0, int64_t &o1)
+{
+    o0 = o1 = 0;
+    uint32_t rem = (uint32_t)idx;
+    for (int i = g.n - 1; i >= 0; i--) {
+        const uint32_t e = (uint32_t)g.ext[i], q = rem / e, k = rem - q * e;
+        rem = q;
+        o0 += (int64_t)k * g.s0[i];
+        o1 += (int64_t)k * g.s1[i];
+    }
+}
+
+// YK: Y is contiguous along k.  VC: columns of a lane (8 or 4) when it is not.
+template <bool YK, int VC>
+__global__ __launch_bounds__(kWaves * 64, 2) void k_contract_rows(const ContractParams p)
+{
+    fetch_params<sizeof(ContractParams)>();
+    constexpr int COLS = YK ? 16 : 16 * VC, KI = YK ? 256 : 32, NL = 8;      // columns of a workgroup, k of an iteration, loads of Y per iteration
+    constexpr int NX = KI / 32;                                              // fragments of X per iteration
+    constexpr int PITCH = COLS + 4;
+    __shared__ __attribute__((aligned(16))) float sums[kWaves][16 * PITCH];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c16 = lane & 15, g = lane >> 4;
+    const int64_t n0 = (int64_t)blockIdx.x * COLS;
+    const int32_t piece = blockIdx.y, M = (int32_t)p.M;
+
+    // this wave's k: a part of the piece, whole iterations of 32 (p.k_stages: k per piece)
+    const int32_t K = (int32_t)p.K, first = piece * p.k_stages, last = first + p.k_stages < K ? first + p.k_stages : K;
+    const int32_t share = ((p.k_stages + kWaves - 1) / kWaves + 31) / 32 * 32;
+    const int32_t kb = first + wave * share, ke = kb + share < last ? kb + share : last;
+
+    // lane offsets in bytes from the wave's first k; a chunk outside is given an offset outside the descriptor and arrives as zeros
+    const int64_t sx = p.k.s0[0], sy = p.k.s1[0];                            // element strides of k
+    int64_t xo, yo, unused;
+    decode(p.m, c16 < M ? c16 : 0, xo, unused);
+    const int64_t col = n0 + (YK ? c16 : VC * c16);
+    const bool inside = col < p.N;                                           // (N is a multiple of VC)
+    decode(p.n, inside ? col : 0, yo, unused);
+    auto uniform = [](const char *q) {
+        const uint64_t v = (uint64_t)q;
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));   // (they return int)
+        return (const char *)(((uint64_t)hi << 32) | lo);
+    };
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void *)uniform((const char *)p.x + (int64_t)kb * sx * 2), 0, (int)0x80000000u, 0x00020000);
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc((void *)uniform((const char *)p.y + (int64_t)kb * sy * 2), 0, (int)0x80000000u, 0x00020000);
+    const uint32_t x0 = (uint32_t)(xo + 8 * g) * 2, y0 = (uint32_t)(yo + 8 * g * sy) * 2, ystep = (uint32_t)sy * 2;
+    const int32_t kn = ke - kb;                                              // may be negative: nothing to do
+
+    u32x4 xf[2][NX], yf[2][NL];
+    auto load = [&](int32_t k, u32x4 (&x)[NX], u32x4 (&y)[NL]) {             // k from the wave's first one
+#pragma unroll
+        for (int j = 0; j < NL; j++) {
+            const int32_t kk = k + 8 * g + (YK ? 32 * j : j);
+            const uint32_t o = inside && kk < kn ? y0 + (uint32_t)(k + (YK ? 32 * j : j)) * ystep : 0x80000000u;
+            if (YK || VC == 8) y[j] = __builtin_amdgcn_raw_buffer_load_b128(ry, (int)o, 0, 2);
+            else {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(ry, (int)o, 0, 2);
+                y[j].x = v.x; y[j].y = v.y;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NX; j++) {
+            const int32_t kk = k + 32 * j;
+            x[j] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(c16 < M && kk + 8 * g < kn ? x0 + (uint32_t)kk * 2 : 0x80000000u), 0, 0);
+        }
+    };
+    constexpr int NF = YK ? 1 : VC;                                          // fragments of 16 columns
+    f32x4 acc[NF];
+#pragma unroll
+    for (int f = 0; f < NF; f++) acc[f] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](const u32x4 (&x)[NX], const u32x4 (&y)[NL]) {
+        if constexpr (YK) {
+#pragma unroll
+            for (int j = 0; j < NL; j++)
+                acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[j]), __builtin_bit_cast(bf16x8, y[j]), acc[0], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int d = 0; d < VC / 2; d++) {                               // columns 2 d and 2 d + 1: eight k each, from eight rows
+                u32x4 lo, hi;
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    lo[j] = __builtin_amdgcn_perm(y[2 * j + 1][d], y[2 * j][d], 0x05040100u);
+                    hi[j] = __builtin_amdgcn_perm(y[2 * j + 1][d], y[2 * j][d], 0x07060302u);
+                }
+                acc[2 * d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[0]), __builtin_bit_cast(bf16x8, lo), acc[2 * d], 0, 0, 0);
+                acc[2 * d + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[0]), __builtin_bit_cast(bf16x8, hi), acc[2 * d + 1], 0, 0, 0);
+            }
+        }
+    };
+    // two iterations in flight; loads behind the last k fetch nothing
+    load(0, xf[0], yf[0]);
+    for (int32_t k = 0; k < kn; k += 2 * KI) {
+        load(k + KI, xf[1], yf[1]);
+        multiply(xf[0], yf[0]);
+        load(k + 2 * KI, xf[0], yf[0]);
+        multiply(xf[1], yf[1]);
+    }
+
+    // lane: column c16 of a fragment, rows 4 g .. 4 g + 3
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        float *s = sums[wave] + (4 * g + r) * PITCH + NF * c16;
+        if constexpr (NF == 1) s[0] = acc[0][r];
+        else {
+#pragma unroll
+            for (int f = 0; f < NF; f += 4) *(f32x4 *)(s + f) = (f32x4){acc[f][r], acc[f + 1][r], acc[f + 2][r], acc[f + 3][r]};
+        }
+    }
+    __syncthreads();
+    char *zb = (char *)p.out.ptr + (p.out.slab_elems ? piece * p.out.slab_elems * 4 : 0);
+    for (int e = tid; e < M * COLS; e += kWaves * 64) {
+        const int m = e / COLS, c = e % COLS;
+        if (n0 + c >= p.N) continue;
+        float s = sums[0][m * PITCH + c];
+#pragma unroll
+        for (int w = 1; w < kWaves; w++) s += sums[w][m * PITCH + c];
+        int64_t zm, zn;
+        decode(p.m, m, unused, zm);
+        decode(p.n, n0 + c, unused, zn);
+        s *= p.alpha;
+        if (p.out.dtype == EG_BF16) ((uint16_t *)zb)[zm + zn] = f32_to_bf16(s);
+        else ((float *)zb)[zm + zn] = s;
+    }
+}
+
+}  // namespace rows
+
+// p: a contraction in one piece (no blocks, no batch label).  The MFMA rows beyond M are idle, and a wave's part of Y has to
+// be long enough to be a stream.
+bool contract_rows_suits(const ContractParams &p)
+{
+    if (p.ragged || p.in_dtype != EG_BF16 || p.otimes != EG_MUL || p.oplus != EG_AGG_SUM) return false;
+    if (p.force_kernel || p.force_tile_m || p.force_waves) return false;
+    if (p.n_tuples != 1 || p.n_batch != 1 || p.k.n != 1 || !p.a_kcontig || p.k.s0[0] != 1) return false;
+    if (p.M > 16 || p.N < 64 || p.K < 256 || p.K >= (1 << 30)) return false;
+    auto span = [](const DimList &g, const int64_t *s) { int64_t t = 0; for (int i = 0; i < g.n; i++) { if (s[i] < 0) return (int64_t)1 << 40; t += (g.ext[i] - 1) * s[i]; } return t; };
+    if (p.k.s1[0] < 1) return false;
+    // 32-bit byte offsets from a wave's first k, iterations past the last one included
+    const int64_t over = p.K + 2048;
+    if (over + span(p.m, p.m.s0) >= (1ll << 30) || over * p.k.s1[0] + span(p.n, p.n.s0) >= (1ll << 30)) return false;
+    if (((uintptr_t)p.x & 15) || ((uintptr_t)p.y & 15)) return false;
+    return true;
+}
+
+// How many pieces the contracted label is cut into, of at most `slabs`, so that every compute unit has a workgroup; and so many that
+// no wave sums up more of it than a slab's block does
+int contract_rows_pieces(const ContractParams &p, int64_t slabs)
+{
+    const int64_t groups = p.b_kcontig ? (p.N + 15) / 16 : (p.N + 63) / 64;
+    int64_t s = groups >= 160 ? 1 : (256 + groups - 1) / groups;         // (8 x 4096 x 11008: 23.1 us in one piece, 22.4 to 26.4 in 2 to 8 and their aggregation)
+    s = std::min(s, std::min(slabs, p.K / 256));
+    return (int)std::max<int64_t>(s, (slabs + rows::kWaves - 1) / rows::kWaves);
+}
+
+int launch_contract_rows(ContractParams &p, int pieces, void *stream)
+{
+    if (!p.x || !p.y || !p.out.ptr) return fail(EG_ERR_NULL, "contraction: NULL operand");
+    if (!contract_rows_suits(p) || pieces < 1 || pieces > 65535 || (pieces > 1) != (p.out.slab_elems != 0)) return fail(EG_ERR_LIMIT, "contraction: shape not eligible for the few-row kernel");
+    p.k_stages = (int32_t)(((p.K + pieces - 1) / pieces + 31) / 32 * 32);
+    // columns per lane: 8, or 4 where that gives too few workgroups
+    const bool wide = (p.N + 127) / 128 * pieces >= 256;
+    const int cols = p.b_kcontig ? 16 : wide ? 128 : 64;
+    const dim3 grid((unsigned)((p.N + cols - 1) / cols), (unsigned)pieces), block(rows::kWaves * 64);
+    hipStream_t st = (hipStream_t)stream;
+    if (p.b_kcontig) EG_LAUNCH((rows::k_contract_rows<true, 8>), grid, block, 0, st, p);
+    else if (wide) EG_LAUNCH((rows::k_contract_rows<false, 8>), grid, block, 0, st, p);
+    else EG_LAUNCH((rows::k_contract_rows<false, 4>), grid, block, 0, st, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(EG_ERR_HIP, "k_contract_rows launch failed: %s", hipGetErrorString(e));
+    return EG_OK;
+}
+
+}  // namespace eg
