@@ -488,17 +488,26 @@ __global__ __launch_bounds__(C::THREADS, C::TOTALS ? 4 : 1) void k_contract(cons
 // ------------------------------------------------------------------------------------------------
 // The same tiling for any other scalar function (x) and reduction (+) of Section 3 of the paper (squared
 // difference with sum, absolute difference with max, ...): no matrix instruction fits, so the tile is worked
-// on the vector ALU.  256 threads as a 16 x 16 grid, each thread an 8 x 8 block of the 128 x 128 tile with
-// rows ty + 16 i and columns tx + 16 j (the 16 lanes that differ in tx read 16 consecutive LDS rows, which the
+// on the vector ALU.  256 threads as a 16 x 16 grid, each thread an 8 x 8 block of the 128 x 128 tile (4 x 4 of
+// 64 x 64) with rows ty + 16 i and columns tx + 16 j (the 16 lanes that differ in tx read 16 consecutive LDS rows, which the
 // swizzle spreads over all banks, and write consecutive columns).  Operands pass through the same loaders and
 // the same LDS layout as above.  The reduction runs over exactly K values: zero-filled tail slots are skipped,
 // since (x)(0, 0) need not be the identity of (+).
 // ------------------------------------------------------------------------------------------------
+// Bound by the issue of vector instructions: two of different waves go out together, so a SIMD whose second wave waits runs at half
+// its rate.  Hence three workgroups per compute unit (168 registers a lane), no instruction right behind the one it waits for, and
+// maxima of two k in one.  8192 x 1024 x 8192 cut 2 x 2 x 2, ms: squared differences 3.55 -> 2.61 (fp32), 3.14 -> 2.54 (bf16),
+// largest absolute difference 2.94 -> 2.16, 2.68 -> 2.19; that is 26 to 32e12 label combinations a second, of 36e12 that a
+// subtract and a multiply-add in registers reach.  Sums of blocks kept in the result instead of slabs (no aggregation, 0.13 ms
+// each) cost the accumulators' registers: 2.89 ms.
+template <typename C, int OT> constexpr int alu_waves() { return C::RAG || OT < 0 ? 2 : 3; }
+
 template <typename C, int OT, int OP>
-__global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractParams p)
+__global__ __launch_bounds__(C::THREADS, (alu_waves<C, OT>())) void k_contract_alu(const ContractParams p)
 {
     fetch_params<sizeof(ContractParams)>();
-    static_assert(C::BM == 128 && C::BN == 128 && C::THREADS == 256, "16 x 16 threads of 8 x 8 outputs");
+    static_assert(C::BM == C::BN && (C::BM == 128 || C::BM == 64) && C::THREADS == 256, "16 x 16 threads of 8 x 8 or 4 x 4 outputs");
+    constexpr int R = C::BM / 16;                            // rows and columns of a thread
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
 
@@ -534,55 +543,107 @@ __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractPa
     la.init(p.x, bx, p.m, m0, p.M, p.a_kcontig != 0, tid);
     lb.init(p.y, by, p.n, n0, p.N, p.b_kcontig != 0, tid);
 
-    float acc[8][8];
+    float acc[R][R];
     const float ident = oplus_identity(OP >= 0 ? OP : p.oplus);
 #pragma unroll
-    for (int i = 0; i < 8; i++)
+    for (int i = 0; i < R; i++)
 #pragma unroll
-        for (int j = 0; j < 8; j++) acc[i][j] = ident;
+        for (int j = 0; j < R; j++) acc[i][j] = ident;
     // Ragged sums carry a compensation term (Kahan), as the one-output-per-lane kernel that took such shapes before did:
     // the same terms in the same order, four more instructions per term.  Only the ragged form has it at all: left unused in
     // the others it stayed in scratch memory where the operators are read at run time (1744 bytes a lane, 1472 without it).
-    constexpr int CN = C::RAG ? 8 : 1;
+    constexpr int CN = C::RAG ? R : 1;
     [[maybe_unused]] float comp[CN][CN];
     if constexpr (C::RAG) {
 #pragma unroll
-        for (int i = 0; i < 8; i++)
+        for (int i = 0; i < R; i++)
 #pragma unroll
-            for (int j = 0; j < 8; j++) comp[i][j] = 0.f;
+            for (int j = 0; j < R; j++) comp[i][j] = 0.f;
     }
 
     const int64_t nk = (p.K + C::BK - 1) / C::BK;
 
+    // element e of a 16-byte chunk
+    auto elem_of = [](const uint4 &v, int e) -> float {
+        const uint32_t w = ((const uint32_t *)&v)[C::BF16 ? e >> 1 : e];
+        return C::BF16 ? __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16)) : __uint_as_float(w);
+    };
     // one 16-byte chunk (EPC consecutive k) of the thread's 8 rows and 8 columns; `valid` k of it count
-    auto chunk = [&](const char *sa, const char *sb, int c, int valid) {
-        uint4 a[8], b[8];
+    [[maybe_unused]] auto chunk = [&](const char *sa, const char *sb, int c, int valid) {
+        uint4 a[R], b[R];
 #pragma unroll
-        for (int i = 0; i < 8; i++) a[i] = *(const uint4 *)(sa + lds_off(ty + 16 * i, c));
+        for (int i = 0; i < R; i++) a[i] = *(const uint4 *)(sa + lds_off(ty + 16 * i, c));
 #pragma unroll
-        for (int j = 0; j < 8; j++) b[j] = *(const uint4 *)(sb + lds_off(tx + 16 * j, c));
+        for (int j = 0; j < R; j++) b[j] = *(const uint4 *)(sb + lds_off(tx + 16 * j, c));
 #pragma unroll
         for (int e = 0; e < C::EPC; e++) {
             if (e >= valid) break;
-            float xs[8], ys[8];
+            float xs[R], ys[R];
 #pragma unroll
-            for (int i = 0; i < 8; i++) {
+            for (int i = 0; i < R; i++) {
                 const uint32_t wa = ((const uint32_t *)&a[i])[C::BF16 ? e >> 1 : e], wb = ((const uint32_t *)&b[i])[C::BF16 ? e >> 1 : e];
                 xs[i] = C::BF16 ? __uint_as_float((e & 1) ? (wa & 0xffff0000u) : (wa << 16)) : __uint_as_float(wa);
                 ys[i] = C::BF16 ? __uint_as_float((e & 1) ? (wb & 0xffff0000u) : (wb << 16)) : __uint_as_float(wb);
             }
 #pragma unroll
-            for (int i = 0; i < 8; i++)
+            for (int i = 0; i < R; i++)
 #pragma unroll
-                for (int j = 0; j < 8; j++) acc[i][j] = oplus_t<OP>(p.oplus, acc[i][j], otimes_t<OT, false>(p.otimes, xs[i], ys[j], p.alpha));
+                for (int j = 0; j < R; j++) acc[i][j] = oplus_t<OP>(p.oplus, acc[i][j], otimes_t<OT, false>(p.otimes, xs[i], ys[j], p.alpha));
             __builtin_amdgcn_sched_barrier(0);       // one k at a time: unpacking all of a chunk ahead of its use costs registers
+        }
+    };
+
+    // The same for the two compiled pairs, a whole chunk.  Four columns at a time: 48 registers of operands instead of 64 let a third
+    // workgroup onto the compute unit.  A row's four differences are taken before the previous row's are used (pinned: as the
+    // compiler orders them, every difference is followed by the instruction that waits for it).
+    // (Row + 64 has the swizzle key of row, so four offsets serve eight rows.)
+    [[maybe_unused]] int pa[4], pb[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) { pa[i] = lds_off(ty + 16 * i, 0); pb[i] = C::LDS_A + lds_off(tx + 16 * i, 0); }
+    [[maybe_unused]] auto whole_chunk = [&](int c) {
+        constexpr bool PAIR = OT == EG_ABSDIFF && OP == EG_AGG_MAX;          // a maximum takes two k in one instruction
+        constexpr int STEP = PAIR ? 2 : 1;
+        uint4 a[R];
+#pragma unroll
+        for (int i = 0; i < R; i++) a[i] = *(const uint4 *)(smem + (pa[i & 3] ^ (c << 4)) + (i >> 2) * 8192);
+#pragma unroll
+        for (int h = 0; h < R / 4; h++) {
+            uint4 b[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) b[j] = *(const uint4 *)(smem + (pb[j] ^ (c << 4)) + h * 8192);
+#pragma unroll
+            for (int e = 0; e < C::EPC; e += STEP) {
+                float d[2][STEP][4];
+                auto differences = [&](int i) {
+#pragma unroll
+                    for (int q = 0; q < STEP; q++) {
+                        const float x = elem_of(a[i], e + q);
+#pragma unroll
+                        for (int j = 0; j < 4; j++) d[i & 1][q][j] = x - elem_of(b[j], e + q);
+                        asm volatile("" : "+v"(d[i & 1][q][0]), "+v"(d[i & 1][q][1]), "+v"(d[i & 1][q][2]), "+v"(d[i & 1][q][3]));
+                    }
+                };
+                differences(0);
+#pragma unroll
+                for (int i = 0; i < R; i++) {
+                    if (i + 1 < R) differences(i + 1);
+#pragma unroll
+                    for (int j = 0; j < 4; j++) {
+                        // (written out: fmaxf makes the compiler quieten the running maximum first, which is never a signalling NaN here)
+                        if constexpr (PAIR) asm volatile("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(acc[i][4 * h + j]) : "v"(d[i & 1][0][j]), "v"(d[i & 1][STEP - 1][j]));
+                        else asm volatile("v_fmac_f32 %0, %1, %1" : "+v"(acc[i][4 * h + j]) : "v"(d[i & 1][0][j]));
+                    }
+                }
+            }
         }
     };
 
     // One LDS stage, no register prefetch: a stage is some ten microseconds of arithmetic per wave, the other
     // workgroups on the compute unit cover the loads, and the registers are needed for the 8 x 8 block.
     const char *sa = smem, *sb = smem + C::LDS_A;
-    for (int64_t kt = 0; kt < nk; kt++) {
+    // (the compiled pairs take whole stages here and the rest behind the loop: with both in it, all accumulators were moved once per chunk)
+    const int64_t nloop = !C::RAG && OT >= 0 ? p.K / C::BK : nk;
+    for (int64_t kt = 0; kt < nloop; kt++) {
         la.fetch(p.k, 0, kt * C::BK, p.K, tid, p.m, p.M);
         lb.fetch(p.k, 1, kt * C::BK, p.K, tid, p.n, p.N);
         la.commit(smem, tid);
@@ -598,13 +659,13 @@ __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractPa
                     const char *q = tile + lds_off(row, k / C::EPC) + (k % C::EPC) * C::ESZ;
                     return C::BF16 ? bf16_to_f32(*(const uint16_t *)q) : *(const float *)q;
                 };
-                float xs[8], ys[8];
+                float xs[R], ys[R];
 #pragma unroll
-                for (int i = 0; i < 8; i++) { xs[i] = elem(sa, ty + 16 * i); ys[i] = elem(sb, tx + 16 * i); }
+                for (int i = 0; i < R; i++) { xs[i] = elem(sa, ty + 16 * i); ys[i] = elem(sb, tx + 16 * i); }
 #pragma unroll
-                for (int i = 0; i < 8; i++)
+                for (int i = 0; i < R; i++)
 #pragma unroll
-                    for (int j = 0; j < 8; j++) {
+                    for (int j = 0; j < R; j++) {
                         const float v = otimes_t<OT, false>(p.otimes, xs[i], ys[j], p.alpha);
                         if ((OP >= 0 ? OP : p.oplus) == EG_AGG_SUM) {
                             const float u = v - comp[i][j], s = acc[i][j] + u;
@@ -615,6 +676,9 @@ __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractPa
                         }
                     }
             }
+        } else if constexpr (OT >= 0) {
+#pragma unroll 1
+            for (int c = 0; c < 8; c++) whole_chunk(c);
         } else if (left >= C::BK) {
 #pragma unroll 1
             for (int c = 0; c < 8; c++) chunk(sa, sb, c, C::EPC);
@@ -623,24 +687,50 @@ __global__ __launch_bounds__(C::THREADS, 2) void k_contract_alu(const ContractPa
         }
         __syncthreads();
     }
+    if constexpr (!C::RAG && OT >= 0) {
+        if (nloop < nk) {
+            la.fetch(p.k, 0, nloop * C::BK, p.K, tid, p.m, p.M);
+            lb.fetch(p.k, 1, nloop * C::BK, p.K, tid, p.n, p.N);
+            la.commit(smem, tid);
+            lb.commit(smem + C::LDS_A, tid);
+            __syncthreads();
+            const int left = (int)(p.K - nloop * C::BK);
+#pragma unroll 1
+            for (int c = 0; c < left / C::EPC; c++) whole_chunk(c);
+#pragma unroll 1
+            for (int k = left / C::EPC * C::EPC; k < left; k++) {
+                auto elem = [&](const char *tile, int row) -> float {
+                    const char *q = tile + lds_off(row, k / C::EPC) + (k % C::EPC) * C::ESZ;
+                    return C::BF16 ? bf16_to_f32(*(const uint16_t *)q) : *(const float *)q;
+                };
+                float xs[R], ys[R];
+#pragma unroll
+                for (int i = 0; i < R; i++) { xs[i] = elem(sa, ty + 16 * i); ys[i] = elem(sb, tx + 16 * i); }
+#pragma unroll
+                for (int i = 0; i < R; i++)
+#pragma unroll
+                    for (int j = 0; j < R; j++) acc[i][j] = oplus_t<OP>(p.oplus, acc[i][j], otimes_t<OT, false>(p.otimes, xs[i], ys[j], p.alpha));
+            }
+        }
+    }
 
     char *zb = (char *)p.out.ptr + (p.out.slab_elems ? agg * p.out.slab_elems * 4 : 0);
     const bool out_bf16 = p.out.dtype == EG_BF16;
-    int64_t zn[8];
+    int64_t zn[R];
 #pragma unroll
-    for (int j = 0; j < 8; j++) {
+    for (int j = 0; j < R; j++) {
         const int64_t n = n0 + tx + 16 * j;
         int64_t unused;
         decode_group(p.n, n < p.N ? n : 0, unused, zn[j]);
     }
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
+    for (int i = 0; i < R; i++) {
         const int64_t m = m0 + ty + 16 * i;
         if (m >= p.M) continue;
         int64_t unused, zm;
         decode_group(p.m, m, unused, zm);
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
+        for (int j = 0; j < R; j++) {
             if (n0 + tx + 16 * j >= p.N) continue;
             const int64_t off = bz + zm + zn[j];
             if (out_bf16) ((uint16_t *)zb)[off] = f32_to_bf16(acc[i][j]);
@@ -671,11 +761,22 @@ static int launch_alu(ContractParams &p, void *stream)
 template <typename C>
 static int launch_alu_ops(ContractParams &p, void *stream)
 {
+    // The compiled pairs: 64 x 64 tiles while there are fewer than two 128 x 128 ones for a compute unit.  A wave alone on its SIMD issues
+    // one instruction in the time of two, and a small launch is as long as a tile (192 x (2 x 192) x 1984 to fp32
+    // 68.3 us with 128 x 128, 30.5 with 64 x 64; 256 x (2 x 512) x 512 158 and 62; 1280 x (2 x 52) x 2304, 360 tiles, 40.4 and 35.1; from 512
+    // on the large ones: 2048 x (2 x 256) x 3072, 768 tiles, 157 and 176).
+    if constexpr (!C::RAG && C::BM == 128) {
+        const int64_t tiles = p.n_tuples * p.n_batch * ((p.M + 127) / 128) * ((p.N + 127) / 128);
+        if (tiles < 512 && ((p.otimes == EG_SQDIFF && p.oplus == EG_AGG_SUM) || (p.otimes == EG_ABSDIFF && p.oplus == EG_AGG_MAX)))
+            return launch_alu_ops<Cfg<64, 64, 32, 32, C::BF16>>(p, stream);
+    }
     // the paper's two examples are compiled in; any other pair reads its operators at run time, which the ragged form does not
     // (9.6 us per contracted element of a tile against 1.0): of others it has the sum of absolute differences only
     if (p.otimes == EG_SQDIFF && p.oplus == EG_AGG_SUM) return launch_alu<C, EG_SQDIFF, EG_AGG_SUM>(p, stream);
     if (p.otimes == EG_ABSDIFF && p.oplus == EG_AGG_MAX) return launch_alu<C, EG_ABSDIFF, EG_AGG_MAX>(p, stream);
-    if constexpr (C::RAG) {
+    if constexpr (C::BM == 64) {
+        return fail(EG_ERR_BAD_OP, "contraction: no 64 x 64 tiles for scalar function %d", p.otimes);
+    } else if constexpr (C::RAG) {
         if (p.otimes == EG_ABSDIFF && p.oplus == EG_AGG_SUM) return launch_alu<C, EG_ABSDIFF, EG_AGG_SUM>(p, stream);
         return fail(EG_ERR_BAD_OP, "contraction: no tiles for scalar function %d of ragged operands", p.otimes);
     } else {
