@@ -337,6 +337,12 @@ static double ragged_tiles_us(const ContractParams &c, int64_t n_tuples)
     }
     const double tiles = (double)((c.M + 63) / 64 * ((c.N + 63) / 64) * c.n_batch * n_tuples);
     double base, stages, us, rate;                            // us per stage of one tile; stages of all tiles per us
+    if (contract_ragged_streams(c)) {                         // (67 shapes of 17 to 3001 rows and columns, 61 to 9001 contracted elements)
+        if (bf && !c.wide) { stages = (double)((c.K + 63) / 64); us = far ? 0.75 : 0.62; rate = 480; }
+        else if (bf) { stages = (double)((c.K + 31) / 32) / 2; us = 2.55; rate = 90; }            // (half a stage at least)
+        else { stages = (double)((c.K + 31) / 32); us = far ? 1.55 : 1.4; rate = 172; }
+        return 7 + std::max(stages * us, tiles * (stages + 0.5) / rate);
+    }
     if (bf && !c.wide) { base = 6.4; stages = (double)((c.K + 63) / 64); us = far ? 1.9 : 1.45; rate = 280; }
     else if (bf) { base = 7; stages = c.K / 64.0; us = far ? 4.8 : 4.25; rate = 81; }          // fp64 instruction, partial stages are cut short
     else { base = 6.5; stages = (double)((c.K + 31) / 32); us = far ? 3.1 : 2.5; rate = 160; }
@@ -361,7 +367,8 @@ static double untiled_us(const Routed &r, const ContractParams &c, int64_t n_tup
         for (int i = 0; i < g.n; i++) span += (g.ext[i] - 1) * g.s0[i];
         return !kcontig && span * (bf ? 2 : 4) > 8000000;
     };
-    const double per_out = c.K < 512 ? outs * 4e-4 : 0;
+    double per_out = c.K < 512 ? outs * 4e-4 : 0;
+    if (!bf && mul && c.a_kcontig && c.b_kcontig) per_out = c.K < 1024 ? outs * 1.7e-4 : 0;   // (201 x 501 x 201 25 us, 111 x 575 x 631 44)
     if (strided(c.a_kcontig, c.k.s0, c.m) || strided(c.b_kcontig, c.k.s1, c.n)) return 5 + per_out + work / (bf ? 0.3 : 0.15);
     if (!mul) return 5 + per_out + work / (bf ? 0.65 : 1.1);
     return 5 + per_out + work / (bf ? (c.K < 4096 ? 1.1 : 0.75) : 1.5);
@@ -1651,16 +1658,17 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
         }
         // Blocks along aggregated labels whose sums the kernel can total itself, where that is faster: no slabs, no aggregation.  (The
         // slabs stay in the workspace's layout, which does not know the strides and addresses that relations are bound with.)
-        if (s.agg && !refined && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && contract_takes_dma(s.r.cp) &&
-            contract_totals_pay(s.r.cp, s.slabs, (int)dtype_size(v.dtype))) {
+        if (s.agg && !refined && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA &&
+            (s.r.ragged ? contract_ragged_totals_pay(s.r.cp, s.slabs, (int)dtype_size(v.dtype))
+                        : contract_takes_dma(s.r.cp) && contract_totals_pay(s.r.cp, s.slabs, (int)dtype_size(v.dtype)))) {
             const OutSpec direct{s.dst, 0, (int32_t)v.dtype};
             Routed rt;
-            if (route(*routed, X, &Y, Z.stride, direct, rt, 1) == EG_OK && rt.kind == EG_KERNEL_CONTRACT_MFMA && !rt.ragged) {
+            if (route(*routed, X, &Y, Z.stride, direct, rt, 1, ragged_sums || L.whole[i] == 2) == EG_OK && rt.kind == EG_KERNEL_CONTRACT_MFMA && rt.ragged == s.r.ragged) {
                 rt.cp.n_totals = (int32_t)s.slabs;
                 rt.cp.n_tuples /= s.slabs;
                 rt.cp.force_kernel = s.r.cp.force_kernel;
                 rt.cp.force_waves = s.r.cp.force_waves;
-                if (contract_takes_dma(rt.cp)) {
+                if (rt.ragged ? contract_ragged_totals_pay(s.r.cp, s.slabs, (int)dtype_size(v.dtype)) : contract_takes_dma(rt.cp)) {
                     s.r = rt;
                     s.agg = false;
                 }

@@ -14,6 +14,7 @@
 // is read so many elements earlier and shifted, and one that crosses into the next run is put together element by element.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <type_traits>
@@ -486,6 +487,319 @@ __global__ __launch_bounds__(C::THREADS, C::TOTALS ? 4 : 1) void k_contract(cons
 }
 
 // ------------------------------------------------------------------------------------------------
+// Ragged products whose contracted label is one run and whose operands' contiguous labels are one run each: 64 x 64 tiles
+// of four waves as above, with loads that need no branches, so that several stages of them can be in flight.  A vector that
+// would cross the end of its run is read so many elements earlier, and moved into place (zeros behind it) on its way into
+// LDS; k-rows past the end are read from the last one and replaced by zeros there.  A workgroup walks over the blocks
+// along the aggregated labels (n_totals) as one sequence of stages, its 64-bit totals go on over all of them.
+//   WIDE (results of 32 bits, fp32 operands): v_mfma_f64_16x16x4, bound by its 64 cycles.  Which k a slot of the instruction
+//       stands for is free, so a lane takes its 16-byte chunks g and g + 4 of a stage's eight whole: 8 LDS reads a stage
+//       instead of 64 of single elements, each followed by the instruction that waits for it.
+//   otherwise (bf16 to bf16): a stage's sums on the bf16 instruction from zero, added to 64-bit totals; bound by the latency of the
+//       loads, of which two stages are in flight (with four, 195 registers and a workgroup fewer on the compute unit: the same).
+// us before (the tiles above: one stage of loads in flight, branches around them) and now: 1000 x 3001 x 1530 to bf16 98 and 52, 1000 x
+// 1530 x 1003 to fp32 123 and 72, 3001 x 1000 x 1530 to fp32 in eight blocks 287 and 215, 1121 x 319 x 647 fp32 33 and 20, 707 x 22867 x
+// 767 in eight 688 and 260; 67 shapes of 17 to 3001 rows and columns 1.3 to 2.6 times as fast.
+// ------------------------------------------------------------------------------------------------
+template <bool BF16, bool WIDE>
+__global__ __launch_bounds__(256, WIDE ? 2 : 3) void k_contract_ragged(const ContractParams p)
+{
+    fetch_params<sizeof(ContractParams)>();
+    constexpr int ES = BF16 ? 2 : 4, EPC = 16 / ES, BK = 128 / ES, NV = 2, CM = 64 / EPC;    // elements per chunk, k of a stage, vectors per thread and operand
+    constexpr int D = 2;                                     // stages in flight
+    constexpr int TILE = 64 * 128;                           // bytes of one operand's stage
+    __shared__ __attribute__((aligned(16))) char lds[2][2 * TILE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+
+    // ---- workgroup -> (output block, batch entry, tile); consecutive logical ids stay on one XCD ----
+    const uint32_t total = gridDim.x, per = total / 8, rem8 = total % 8, xcd = blockIdx.x % 8;
+    const uint32_t logical = xcd * per + (xcd < rem8 ? xcd : rem8) + blockIdx.x / 8;
+    const uint32_t tiles = (uint32_t)p.tiles_m * (uint32_t)p.tiles_n, tb = logical / tiles, tl = logical - tb * tiles;
+    constexpr uint32_t GM = 8;                               // tile rows walked together for L2 reuse
+    const uint32_t span = GM * (uint32_t)p.tiles_n, grp = tl / span, first_m = grp * GM;
+    const uint32_t gsz = (uint32_t)p.tiles_m - first_m < GM ? (uint32_t)p.tiles_m - first_m : GM;
+    const int64_t m0 = (int64_t)(first_m + (tl - grp * span) % gsz) * 64, n0 = (int64_t)((tl - grp * span) / gsz) * 64;
+    const uint32_t tuple = tb / (uint32_t)p.n_batch, bidx = tb - tuple * (uint32_t)p.n_batch;
+    const uint32_t blocks = p.n_totals > 1 ? (uint32_t)p.n_totals : 1u;
+    int64_t bx, by, bz, agg = 0;
+    if (blocks > 1) group_offsets(p.ts, tuple, bx, by, bz);
+    else decode_tuple(p.ts, tuple, bx, by, bz, agg);
+    {
+        uint32_t rem = bidx;
+        for (int i = p.batch.n - 1; i >= 0; i--) {
+            const uint32_t e = (uint32_t)p.batch.ext[i], q = rem / e, k = rem - q * e;
+            rem = q;
+            bx += (int64_t)k * p.batch.s0[i];
+            by += (int64_t)k * p.batch.s1[i];
+            bz += (int64_t)k * p.batch.s2[i];
+        }
+    }
+
+    // ---- one operand's side of the loads ----
+    const int32_t K = (int32_t)p.K;
+    struct Side {
+        int64_t off[NV];                                     // element offset of the row (along k) or of the chunk (otherwise, off[0])
+        int64_t ks;                                          // element stride of k
+        int32_t k;                                           // first k of this thread's vectors inside a stage
+        int32_t back;                                        // chunk at the edge, read so many elements earlier
+        bool kc;
+    };
+    auto side = [&](const DimList &g, int64_t first, int64_t extent, bool kc, int64_t ks) {
+        Side d;
+        d.kc = kc;
+        d.ks = ks;
+        d.back = 0;
+        int64_t unused;
+        if (kc) {
+            d.k = (tid & 7) * EPC;
+#pragma unroll
+            for (int i = 0; i < NV; i++) {
+                const int64_t r = first + (tid >> 3) + i * 32;
+                decode_group(g, r < extent ? r : extent - 1, d.off[i], unused);      // rows past the edge are never stored
+            }
+        } else {
+            d.k = tid / CM * NV;
+            int64_t m = first + (int64_t)(tid % CM) * EPC;
+            m = m < extent ? m : extent - 1;
+            if (m + EPC > extent) { d.back = (int32_t)(m + EPC - extent); m = extent - EPC; }
+            decode_group(g, m, d.off[0], unused);
+            d.off[1] = 0;
+        }
+        return d;
+    };
+    const Side A = side(p.m, m0, p.M, p.a_kcontig != 0, p.k.s0[0]), B = side(p.n, n0, p.N, p.b_kcontig != 0, p.k.s1[0]);
+    const char *xt = (const char *)p.x + bx * ES, *yt = (const char *)p.y + by * ES;
+    auto load_side = [&](const Side &d, const char *base, int32_t k0, uint4 (&v)[NV]) {
+        if (d.kc) {
+            int32_t k = k0 + d.k;
+            k = k + EPC <= K ? k : K - EPC;
+#pragma unroll
+            for (int i = 0; i < NV; i++) v[i] = load_elem_aligned<BF16>(base + (d.off[i] + k) * ES);
+        } else {
+#pragma unroll
+            for (int i = 0; i < NV; i++) {
+                int32_t k = k0 + d.k + i;
+                k = k < K ? k : K - 1;
+                v[i] = load_elem_aligned<BF16>(base + (d.off[0] + (int64_t)k * d.ks) * ES);
+            }
+        }
+    };
+    // a stage's vectors into LDS; whole: all of its k exist
+    auto store_side = [&](const Side &d, int32_t k0, bool whole, bool edge, uint4 (&v)[NV], char *tile) {
+        if (d.kc) {
+            if (!whole) {
+                const int32_t over = k0 + d.k + EPC - K;     // elements behind the last k
+#pragma unroll
+                for (int i = 0; i < NV; i++)
+                    if (over > 0) v[i] = over < EPC ? drop_elems<BF16>(v[i], over) : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < NV; i++) *(uint4 *)(tile + lds_off((tid >> 3) + i * 32, tid & 7)) = v[i];
+        } else {
+            if (edge) {
+#pragma unroll
+                for (int i = 0; i < NV; i++) v[i] = drop_elems<BF16>(v[i], d.back);
+            }
+            if (!whole) {
+#pragma unroll
+                for (int i = 0; i < NV; i++)
+                    if (k0 + d.k + i >= K) v[i] = make_uint4(0, 0, 0, 0);
+            }
+            transpose_store<NV, BF16>(v, tile, (tid % CM) * EPC, d.k);
+        }
+    };
+    const bool edge_a = !A.kc && m0 + 64 > p.M, edge_b = !B.kc && n0 + 64 > p.N;
+
+    // ---- stages: the loads run D stages ahead of the arithmetic, over the ends of blocks; past the last stage they repeat it ----
+    const int32_t per_block = (K + BK - 1) / BK;
+    const int64_t nst = (int64_t)per_block * blocks;
+    uint32_t lblk = 0;
+    int32_t lk = 0, sk = 0;                                  // next stage to load (block, first k); next one to store
+    const char *xl = xt, *yl = yt;
+    int64_t loaded = 0;
+    if (blocks > 1) {
+        int64_t ox, oy;
+        agg_offsets(p.ts, 0, ox, oy);
+        xl = xt + ox * ES;
+        yl = yt + oy * ES;
+    }
+    auto load = [&](uint4 (&a)[NV], uint4 (&b)[NV]) {
+        load_side(A, xl, lk, a);
+        load_side(B, yl, lk, b);
+        if (++loaded < nst) {
+            lk += BK;
+            if (lk >= K) {
+                lk = 0;
+                lblk++;
+                int64_t ox, oy;
+                agg_offsets(p.ts, lblk, ox, oy);
+                xl = xt + ox * ES;
+                yl = yt + oy * ES;
+            }
+        }
+    };
+    auto store = [&](uint4 (&a)[NV], uint4 (&b)[NV], char *dst) {
+        const bool whole = sk + BK <= K;
+        store_side(A, sk, whole, edge_a, a, dst);
+        store_side(B, sk, whole, edge_b, b, dst + TILE);
+        sk = sk + BK < K ? sk + BK : 0;
+    };
+
+    uint4 ra[D][NV], rb[D][NV];
+#pragma unroll
+    for (int d = 0; d < D; d++) load(ra[d], rb[d]);
+    store(ra[0], rb[0], lds[0]);
+    load(ra[0], rb[0]);
+    __syncthreads();
+
+    constexpr int AR = WIDE ? 4 : 16;
+    typedef double totals __attribute__((ext_vector_type(AR)));
+    constexpr int MT = WIDE ? 2 : 1;
+    totals acc[MT][MT];
+#pragma unroll
+    for (int i = 0; i < MT; i++)
+#pragma unroll
+        for (int j = 0; j < MT; j++)
+#pragma unroll
+            for (int r = 0; r < AR; r++) acc[i][j][r] = 0;
+    const int c16 = lane & 15, g = lane >> 4, lrow = lane & 31, lhalf = lane >> 5;
+    int32_t ck = 0;                                          // first k of the stage that is multiplied
+    [[maybe_unused]] uint4 wa[2][2], wb[2][2];               // WIDE: row or column tile, chunk g or g + 4
+    [[maybe_unused]] auto fragments = [&](const char *buf, int h) {
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            wa[i][h] = *(const uint4 *)(buf + lds_off(wm * 32 + i * 16 + c16, g + 4 * h));
+            wb[i][h] = *(const uint4 *)(buf + TILE + lds_off(wn * 32 + i * 16 + c16, g + 4 * h));
+        }
+    };
+    [[maybe_unused]] auto half = [&](int h) {
+        if constexpr (WIDE) {
+            auto elem = [](const uint4 &v, int e) -> double {
+                const uint32_t w = ((const uint32_t *)&v)[BF16 ? e >> 1 : e];
+                return BF16 ? (double)__uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16)) : (double)__uint_as_float(w);
+            };
+#pragma unroll
+            for (int e = 0; e < EPC; e++) {
+                double x[2], y[2];
+#pragma unroll
+                for (int i = 0; i < 2; i++) { x[i] = elem(wa[i][h], e); y[i] = elem(wb[i][h], e); }
+#pragma unroll
+                for (int i = 0; i < 2; i++)
+#pragma unroll
+                    for (int j = 0; j < 2; j++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i], y[j], acc[i][j], 0, 0, 0);
+            }
+        }
+    };
+    if constexpr (WIDE) {
+        fragments(lds[0], 0);
+        fragments(lds[0], 1);
+    }
+    auto stage = [&](const char *cur, char *nxt, uint4 (&a)[NV], uint4 (&b)[NV]) {
+        const char *sa = cur, *sb = cur + TILE;
+        if constexpr (WIDE) {
+            // the fragments were read under the MFMAs of the stage before, half of them (chunks g, chunks g + 4) at a time, so that
+            // a wave alone on its SIMD does not wait for them
+            store(a, b, nxt);
+            load(a, b);
+            half(0);
+            const bool second = ck + BK / 2 < K;             // (chunks 4 to 7 of a last stage may hold zeros only)
+            __syncthreads();
+            fragments(nxt, 0);
+            if (second) half(1);
+            fragments(nxt, 1);
+            ck = ck + BK < K ? ck + BK : 0;
+            return;
+        } else {
+            uint4 fa[4], fb[4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ks++) {
+                fa[ks] = *(const uint4 *)(sa + lds_off(wm * 32 + lrow, 2 * ks + lhalf));
+                fb[ks] = *(const uint4 *)(sb + lds_off(wn * 32 + lrow, 2 * ks + lhalf));
+            }
+            f32x16 part;
+#pragma unroll
+            for (int r = 0; r < 16; r++) part[r] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 4; ks++)
+                part = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)&fa[ks], *(const bf16x8 *)&fb[ks], part, 0, 0, 0);
+            store(a, b, nxt);
+            load(a, b);
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[0][0][r] += (double)part[r];
+        }
+        ck = ck + BK < K ? ck + BK : 0;
+        __syncthreads();
+    };
+    for (int64_t st = 0; st < nst; st += D) {
+#pragma unroll
+        for (int d = 0; d < D; d++) {
+            if (st + d >= nst) break;
+            stage(lds[d & 1], lds[(d + 1) & 1], ra[(d + 1) % D], rb[(d + 1) % D]);
+        }
+    }
+
+    // ---- epilogue: lane holds column (lane % 32) and rows 8*(r/4) + 4*(lane/32) + r%4 of its 32x32 tile; WIDE: column lane % 16
+    // and rows 4*r + lane/16 of each 16x16 tile ----
+    char *zb = (char *)p.out.ptr + (p.out.slab_elems ? agg * p.out.slab_elems * 4 : 0);
+#pragma unroll
+    for (int j = 0; j < MT; j++) {
+        const int64_t n = n0 + wn * 32 + (WIDE ? j * 16 + c16 : lrow);
+        if (n >= p.N) continue;
+        int64_t unused, zn;
+        decode_group(p.n, n, unused, zn);
+#pragma unroll
+        for (int i = 0; i < MT; i++)
+#pragma unroll
+            for (int r = 0; r < AR; r++) {
+                const int64_t m = m0 + wm * 32 + (WIDE ? i * 16 + 4 * r + g : 8 * (r >> 2) + 4 * lhalf + (r & 3));
+                if (m >= p.M) continue;
+                int64_t zm;
+                decode_group(p.m, m, unused, zm);
+                const float val = (float)((double)p.alpha * acc[i][j][r]);
+                const int64_t off = bz + zm + zn;
+                if (p.out.dtype == EG_BF16) ((uint16_t *)zb)[off] = f32_to_bf16(val);
+                else ((float *)zb)[off] = val;
+            }
+    }
+}
+
+// operands the kernel above takes: one run each along the contracted label and along what they are contiguous in, a chunk at least
+bool contract_ragged_streams(const ContractParams &p)
+{
+    if (!p.ragged || p.otimes != EG_MUL || p.oplus != EG_AGG_SUM || p.k.n != 1) return false;
+    const int epc = p.in_dtype == EG_BF16 ? 8 : 4;
+    if (p.K < epc || p.K >= (1ll << 30)) return false;
+    return (p.a_kcontig || (p.m.n == 1 && p.M >= epc)) && (p.b_kcontig || (p.n.n == 1 && p.N >= epc));
+}
+
+// Do they run faster with a tile's blocks one after another in one workgroup than each with its own, slabs and an aggregation?
+// A stage takes 2.5 us on the fp64 instruction (fp32 operands 1.4), 0.6 on the bf16 one.  (3001 x (8 x 125) x 1530 to fp32: 259 us and
+// 28 for the aggregation through slabs, 215 without; 1530 x (8 x 125) x 1003 98 and 12, 92.)
+bool contract_ragged_totals_pay(const ContractParams &p, int64_t n_agg, int out_bytes)
+{
+    if (n_agg < 2 || n_agg > INT32_MAX || p.n_tuples % n_agg || !contract_ragged_streams(p)) return false;
+    const double outs = (double)(p.n_tuples / n_agg * p.n_batch), tiles = outs * ((p.M + 63) / 64) * ((p.N + 63) / 64), n = (double)n_agg;
+    const int bk = p.in_dtype == EG_BF16 ? 64 : 32;
+    const double stages = (double)((p.K + bk - 1) / bk) * (!p.wide ? 0.6 : p.in_dtype == EG_BF16 ? 2.5 : 1.4);
+    return std::max(tiles / 256, 1.0) * stages * n < std::max(tiles * n / 256, 1.0) * (stages + 1) + 5 + outs * p.M * p.N * (4 * n + out_bytes) / 5.3e6;
+}
+
+static int launch_ragged_streams(ContractParams &p, void *stream)
+{
+    p.tiles_m = (int32_t)((p.M + 63) / 64);
+    p.tiles_n = (int32_t)((p.N + 63) / 64);
+    const int64_t wgs = p.n_tuples * p.n_batch * p.tiles_m * p.tiles_n;
+    if (wgs < 1 || wgs >= (1ll << 31)) return fail(EG_ERR_LIMIT, "contraction needs %lld workgroups", (long long)wgs);
+    const dim3 grid((unsigned)wgs), block(256);
+    if (!p.wide) EG_LAUNCH((k_contract_ragged<true, false>), grid, block, 0, (hipStream_t)stream, p);
+    else if (p.in_dtype == EG_BF16) EG_LAUNCH((k_contract_ragged<true, true>), grid, block, 0, (hipStream_t)stream, p);
+    else EG_LAUNCH((k_contract_ragged<false, true>), grid, block, 0, (hipStream_t)stream, p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(EG_ERR_HIP, "k_contract_ragged launch failed: %s", hipGetErrorString(e));
+    return EG_OK;
+}
+
+// ------------------------------------------------------------------------------------------------
 // The same tiling for any other scalar function (x) and reduction (+) of Section 3 of the paper (squared
 // difference with sum, absolute difference with max, ...): no matrix instruction fits, so the tile is worked
 // on the vector ALU.  256 threads as a 16 x 16 grid, each thread an 8 x 8 block of the 128 x 128 tile (4 x 4 of
@@ -823,17 +1137,22 @@ bool contract_takes_dma(const ContractParams &p)
 // on the fp64 matrix instruction, exact products and 64-bit sums.  64 x 64 tiles throughout: the 64-bit totals take 128
 // registers of a 128 x 128 tile's lanes, and with one wave per SIMD left, or two of half the tile, nothing hides the loads
 // (4001 x 3001 x 4099: 447 us with 64 x 64, 557 with 128 x 64, 592 with 128 x 128; 439 with 128 x 128 and plain fp32 sums).
-// Measured against one output per lane: fp32 1121 x 319 x 646 371 -> 36 us; bf16 chain 1043 x 437 x 293 x 1156 1002 -> 60 us;
-// a classifier's step of 1000 x 3001 x 1530 x 1003 23.5 -> 0.72 ms (1000 x 3001 x 1530 to bf16 97 us, 95 TFLOP/s: a stage's
-// loads wait behind one another in 384 tiles; 3001 x 1000 x 1530 to fp32 in eight slabs 266 us, 35 of the fp64 matrix
-// instruction's 78 TFLOP/s, with two stages per tile).
+// Operands of one run each take k_contract_ragged; the forms with run-by-run loads are left for the others (two contracted labels that
+// do not join, runs of a few elements).  Against one output per lane, which ran such shapes before there were tiles: fp32
+// 1121 x 319 x 646 371 us, 20 now; a classifier's step of 1000 x 3001 x 1530 x 1003 23.5 ms, 0.50 now.
 static int launch_ragged(ContractParams &p, void *stream)
 {
     if (p.otimes != EG_MUL || p.oplus != EG_AGG_SUM) {
+        if (p.n_totals > 1) return fail(EG_ERR_LIMIT, "contraction: no totals of blocks on this form");
         if (p.otimes < EG_MUL || p.otimes > EG_SILU_MUL) return fail(EG_ERR_BAD_OP, "contraction: scalar function %d is not binary", p.otimes);
         if (p.in_dtype == EG_BF16) return launch_alu_ops<Cfg<128, 128, 64, 64, true, true>>(p, stream);
         return launch_alu_ops<Cfg<128, 128, 64, 64, false, true>>(p, stream);
     }
+    if (contract_ragged_streams(p)) {
+        if (!p.wide && p.in_dtype != EG_BF16) return fail(EG_ERR_LIMIT, "contraction: ragged fp32 operands are summed in 64 bits");
+        return launch_ragged_streams(p, stream);
+    }
+    if (p.n_totals > 1) return fail(EG_ERR_LIMIT, "contraction: no totals of blocks on this form");
     if (p.wide) {
         if (p.in_dtype == EG_BF16) return launch_cfg<Cfg<64, 64, 32, 32, true, true, true>>(p, stream);
         return launch_cfg<Cfg<64, 64, 32, 32, false, true, true>>(p, stream);

@@ -1,0 +1,76 @@
+"""Ragged products whose operands are one run each (k_contract_ragged): contracted labels around half a stage, a stage and the depth
+of the prefetch, rows and columns around a chunk and a tile in every layout, operands inside tensors of NaN, and blocks along the
+contracted label that one workgroup walks over (no aggregation launch; totals in 64 bits over all of them)."""
+import numpy as np
+import pytest
+
+from tests._parity import RTOL_BF16, RTOL_F32, single_vertex, violations
+from oracle.graph_ref import run_graph
+from synth_inputs.prng import HostTensor, uniform_pm1
+
+pytestmark = pytest.mark.gpu
+
+LAYOUTS = ["ij,jk->ik", "ij,kj->ik", "ji,jk->ik", "ji,kj->ik"]
+TYPES = [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32")]
+# rows, columns, contracted
+SIZES = [(65, 63, 17), (77, 129, 33), (9, 513, 63), (130, 67, 65), (64, 67, 97), (201, 73, 127), (67, 64, 129), (71, 61, 257), (65, 129, 515)]
+
+
+def _run(w, x, y, pad=False, tiled=None):
+    import torch
+    import paper_2410_02682_amd as E
+    from paper_2410_02682_amd.runner import GraphRunner, to_device, to_host
+
+    def bound(t):
+        t = to_device(t)
+        if not pad:
+            return t
+        big = torch.full(tuple(t.shape[:-1]) + (t.shape[-1] + 5,), float("nan"), dtype=t.dtype, device="cuda")
+        view = big[..., 3:-2]
+        view.copy_(t)
+        return view
+
+    r = GraphRunner(w, "d", tiled_partials=tiled)
+    try:
+        r.bind({"X": bound(x), "Y": bound(y)})
+        kernel = r.plan("Z")["kernel"]
+        E.tr_profile_enable(r.g, 8)
+        r.run()
+        torch.cuda.synchronize()
+        return to_host(r.output("Z")).as_f64(), kernel, [q["stage"] for q in E.tr_profile_read(r.g)]
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("dt,odt", TYPES)
+@pytest.mark.parametrize("spec", LAYOUTS)
+@pytest.mark.parametrize("m,n,k", SIZES)
+def test_edges_of_stages_and_tiles(m, n, k, spec, dt, odt):
+    print(f"ragged {spec} {m} x {k} x {n} {dt}->{odt}", flush=True)
+    ext = {"i": m, "j": k, "k": n}
+    x, y = (HostTensor.from_f32(uniform_pm1(67, p, int(np.prod(b))).reshape(b), dt) for p, b in enumerate(tuple(ext[l] for l in o) for o in spec.split("->")[0].split(",")))
+    w = single_vertex(spec, x, y, odt, alpha=-1.5, parts={"d": {}})
+    ref = run_graph(w, {"X": x, "Y": y})["Z"].as_f64()
+    for pad in (False, True):
+        got, _, _ = _run(w, x, y, pad)
+        bad, worst = violations(got, ref, RTOL_BF16 if odt == "bf16" else RTOL_F32)
+        assert bad == 0, f"padded {pad}: {bad} elements out of tolerance (worst {worst:.2f}x)"
+
+
+@pytest.mark.parametrize("spec,bx,by,part,dt,odt", [
+    ("ij,jk->ik", (1027, 8 * 41), (8 * 41, 1101), {"j": 8}, "bf16", "f32"),
+    ("ij,kj->ik", (1027, 3 * 131), (1101, 3 * 131), {"j": 3}, "bf16", "bf16"),
+    ("ji,jk->ik", (2 * 65, 1027), (2 * 65, 1101), {"j": 2}, "f32", "f32"),
+    ("bij,bjk->bik", (3, 517, 5 * 27), (3, 5 * 27, 643), {"j": 5, "b": 3}, "bf16", "f32"),
+    ("ijl,jlk->ik", (1027, 6, 35), (6, 35, 1101), {"j": 3}, "bf16", "f32"),                 # blocks of two joined labels
+])
+def test_blocks_along_the_contracted_label(spec, bx, by, part, dt, odt):
+    print(f"ragged blocks {spec} X{bx} Y{by} d {part} {dt}->{odt}", flush=True)
+    x, y = (HostTensor.from_f32(uniform_pm1(71, p, int(np.prod(b))).reshape(b), dt) for p, b in enumerate((bx, by)))
+    w = single_vertex(spec, x, y, odt, parts={"d": part})
+    ref = run_graph(w, {"X": x, "Y": y})["Z"].as_f64()
+    for tiled, stages in ((True, ["join"]), (False, ["join", "aggregate"])):
+        got, kernel, launches = _run(w, x, y, tiled=tiled)
+        assert kernel == "contract_mfma" and launches == stages, (kernel, launches)
+        bad, worst = violations(got, ref, RTOL_BF16 if odt == "bf16" else RTOL_F32)
+        assert bad == 0, f"tiled {tiled}: {bad} elements out of tolerance (worst {worst:.2f}x)"
