@@ -11,7 +11,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libeindecomp.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["eg_graph.cpp", "eg_planner.cpp", "eg_exec.hip", "k_simple.hip", "k_contract.hip", "k_contract_dma.hip", "k_contract_dma_256.hip",
-           "k_contract_dma_128.hip", "k_contract_dma_totals.hip", "k_contract_rows.hip", "k_attention.hip", "k_ceilings.hip"]
+           "k_contract_dma_128.hip", "k_contract_dma_totals.hip", "k_contract_dma_carry.hip", "k_contract_rows.hip", "k_attention.hip", "k_ceilings.hip"]
 HEADERS = [os.path.join(CSRC, "eg_internal.h"), os.path.join(CSRC, "eg_device.h"), os.path.join(CSRC, "k_contract_dma.h"), os.path.join(INCLUDE, "eindecomp.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE, "-I" + CSRC,
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",

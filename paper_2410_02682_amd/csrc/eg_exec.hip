@@ -1656,6 +1656,23 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
                 }
             }
         }
+        // Two long blocks: a tile's sums wait in the first slab while its second block is multiplied; no aggregation.
+        if (s.agg && !refined && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && s.partials && contract_takes_dma(s.r.cp) &&
+            contract_carry_pays(s.r.cp, s.slabs)) {
+            const OutSpec direct{s.dst, 0, (int32_t)v.dtype};
+            Routed rt;
+            if (route(*routed, X, &Y, Z.stride, direct, rt, 1, ragged_sums || L.whole[i] == 2) == EG_OK && rt.kind == EG_KERNEL_CONTRACT_MFMA && !rt.ragged) {
+                rt.cp.n_totals = 2;
+                rt.cp.n_tuples /= 2;
+                rt.cp.carry = (float *)s.partials;
+                rt.cp.force_kernel = s.r.cp.force_kernel;
+                rt.cp.force_waves = s.r.cp.force_waves;
+                if (rt.cp.M % 256 == 0 && rt.cp.N % 256 == 0 && contract_takes_dma(rt.cp) && rt.cp.n_tuples * rt.cp.n_batch * rt.cp.M * rt.cp.N == numel(v.bound)) {
+                    s.r = rt;
+                    s.agg = false;
+                }
+            }
+        }
         // Blocks along aggregated labels whose sums the kernel can total itself, where that is faster: no slabs, no aggregation.  (The
         // slabs stay in the workspace's layout, which does not know the strides and addresses that relations are bound with.)
         if (s.agg && !refined && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA &&

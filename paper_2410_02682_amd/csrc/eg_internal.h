@@ -67,12 +67,13 @@ struct ContractParams {
     OutSpec out;
     int64_t n_tuples;
     int64_t span_x, span_y;       // largest element offset inside one block of X / Y
+    float *carry;                 // n_totals == 2, 256 x 256 tiles: where the first block's sums wait for the second's (64 Ki floats per tile)
     int32_t tiles_m, tiles_n;     // filled by the launcher
     int32_t out_vec;              // filled by the launcher: 1 = Z rows can be written as 16-byte vectors along N
     int32_t total_tiles, grid;    // filled by the launcher: output tiles over all tuples and batch entries; workgroups that share them
-    int32_t force_kernel;         // 0: the launcher chooses; 1: register-staged kernel; 2: direct-to-LDS kernel wherever the layout allows (tr_set_contract_variant)
-    int32_t force_tile_m, force_tile_n;   // 0: the launcher chooses; 128 x 128, 256 x 128 or 256 x 256: tile of the direct-to-LDS kernel
-    int32_t force_waves;          // 0: the launcher chooses; 4 / 8: waves per workgroup of the 256 x 256 direct-to-LDS kernel
+    int16_t force_kernel;         // 0: the launcher chooses; 1: register-staged kernel; 2: direct-to-LDS kernel wherever the layout allows (tr_set_contract_variant)
+    int16_t force_tile_m, force_tile_n;   // 0: the launcher chooses; 128 x 128, 256 x 128 or 256 x 256: tile of the direct-to-LDS kernel
+    int16_t force_waves;          // 0: the launcher chooses; 4 / 8: waves per workgroup of the 256 x 256 direct-to-LDS kernel
     int32_t tile_order;           // 1: partial slabs are written tile after tile in the accumulators' order (see AggTilesParams)
     int32_t k_stages;             // filled by the launcher of the direct-to-LDS kernel: stages per output tile
     int32_t n_totals;             // > 1: the kernel walks over this many blocks along the aggregated labels and keeps the totals of their sums; n_tuples counts output blocks then
@@ -259,6 +260,7 @@ bool contract_rows_suits(const ContractParams &p);                             /
 int contract_rows_pieces(const ContractParams &p, int64_t slabs);
 int launch_contract_rows(ContractParams &p, int pieces, void *stream);
 bool contract_totals_pay(const ContractParams &p, int64_t n_agg, int out_bytes);   // ... and faster with totals kept in the kernel than through partial slabs
+bool contract_carry_pays(const ContractParams &p, int64_t n_agg);
 size_t attention_mask_class_bytes(int64_t S, int64_t T);
 
 // ------------------------------------------------------------------------------------------------

@@ -231,10 +231,13 @@ constexpr int lds_bytes(int TM, int TN, int KB, int WM, int NW, int NS)
 }
 
 // NS: LDS stages (2 or 3); REM: the stage count modulo NS.
+// MODE 1: one tile over n_totals blocks, whose totals stay in registers; 2: as 0, but a tile's two
+// blocks follow one another and the first one's sums wait in memory (p.carry) for the second.
 // Four stages (KG = 2): two groups of waves share the tile, each takes half of a stage's k-steps.
-template <int TM, int TN, int KB, int NS, int WM, int NW, bool A_KC, bool B_KC, int REM, bool F32, bool TOT>
+template <int TM, int TN, int KB, int NS, int WM, int NW, bool A_KC, bool B_KC, int REM, bool F32, int MODE>
 __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 160 * 1024 ? 2 : 1) void k_contract_dma(const ContractParams p)
 {
+    constexpr bool TOT = MODE == 1, CARRY = MODE == 2;
     constexpr int ES = Elem<F32>::ES, EPC = Elem<F32>::EPC, BK = KB / ES;
     constexpr int KS = KB / 32;                       // k-steps per stage (32 bytes of k each)
     constexpr int KG = NS == 4 ? 2 : 1;               // groups of waves, each with the whole tile and its own k-steps of a stage
@@ -279,6 +282,7 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
         count = first < total ? (total - first + G - 1) / G : 0;
     }
     if (count == 0) return;
+    if (CARRY) count *= 2;                            // (a tile's two blocks one after the other)
 
     auto uniform_ptr = [](const char *q) {            // the buffer descriptors must live in scalar registers
         const uint64_t v = (uint64_t)q;
@@ -286,7 +290,9 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
         return (const char *)(((uint64_t)hi << 32) | lo);
     };
     // logical id -> (tuple, batch entry, tile); tiles are walked in groups of 8 tile rows
-    auto tile_info = [&](uint32_t logical, TileInfo &t) {
+    auto tile_info = [&](uint32_t it, TileInfo &t) {
+        const uint32_t walk = CARRY ? it / 2 : it, block = CARRY ? it % 2 : 0;
+        const uint32_t logical = first + walk * stride;
         const uint32_t tiles = (uint32_t)p.tiles_m * (uint32_t)p.tiles_n;
         const uint32_t tb = logical / tiles, tl = logical - tb * tiles;
         constexpr uint32_t GM = 8;
@@ -297,8 +303,15 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
         const uint32_t tile_n = (tl - grp * span) / gsz;
         const uint32_t nb = (uint32_t)p.n_batch, tuple = tb / nb, bidx = tb - tuple * nb;
         int64_t bx, by, bz, agg = 0;
-        if (TOT) group_offsets(p.ts, tuple, bx, by, bz);
+        if (MODE) group_offsets(p.ts, tuple, bx, by, bz);
         else decode_tuple(p.ts, tuple, bx, by, bz, agg);
+        if constexpr (CARRY) {
+            int64_t ox, oy;
+            agg_offsets(p.ts, block, ox, oy);
+            bx += ox;
+            by += oy;
+            agg = block;
+        }
         uint32_t rem = bidx;
         for (int i = p.batch.n - 1; i >= 0; i--) {
             uint32_t e = (uint32_t)p.batch.ext[i], q = rem / e, k = rem - q * e;
@@ -319,7 +332,8 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
         t.yb = uniform_ptr((const char *)p.y + (by + t.oy0) * ES);
         t.bz = bz;
         t.agg = agg;
-        t.slab_tile = p.tile_order ? ((tuple_group(p.ts, tuple) * nb + bidx) * (int64_t)p.tiles_m + tile_m) * (int64_t)p.tiles_n + tile_n : 0;
+        if (CARRY) t.slab_tile = (int64_t)tb * tiles + tile_m * (uint32_t)p.tiles_n + tile_n;
+        else t.slab_tile = p.tile_order ? ((tuple_group(p.ts, tuple) * nb + bidx) * (int64_t)p.tiles_m + tile_m) * (int64_t)p.tiles_n + tile_n : 0;
     };
     const int kin = p.k.n - 1;                        // innermost K label: every stage lies inside one run of it
     const int32_t run = p.k.n == 1 ? (int32_t)p.K : p.k.ext[kin];   // k of one run of the innermost K label
@@ -572,15 +586,15 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
         }
     };
     const bool out_bf16 = p.out.dtype == EG_BF16;
-    const float alpha = TOT ? 1.f : p.alpha;          // (totals are scaled already)
+    const float alpha = MODE ? 1.f : p.alpha;         // (totals are scaled already)
 
-    tile_info(first, cur);
+    tile_info(0, cur);
     start_tile(cur);
     for (uint32_t it = 0;; it++) {
         const bool more = it + 1 < count;
         // while the first stages travel: the next tile's uniform addressing and this tile's Z offset tables
         // (256 rows, 256 columns; two sets in turn, so a wave already in the next tile cannot disturb a slower one)
-        if (more) tile_info(first + (it + 1) * stride, nxt);
+        if (more) tile_info(it + 1, nxt);
         int64_t *zrow = (int64_t *)(ldsx + (it & 1) * TBL), *zcol = zrow + TM;
         if (!p.tile_order)                            // (tile-ordered partial slabs need no Z offsets)
         for (int e = tid; e < TM + TN; e += NW * 64) {
@@ -714,7 +728,43 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
         const bool slab = p.out.slab_elems != 0;
         const int mrem = (int)(p.M - cur.m0 < TM ? p.M - cur.m0 : TM);     // rows / columns of the tile inside the block
         const int nrem = (int)(p.N - cur.n0 < TN ? p.N - cur.n0 : TN);
-        if (KG == 1 && p.tile_order) {
+        bool carried = false;
+        if constexpr (CARRY) {
+            // The first block's sums, scaled and rounded as its partial slab would have held them, wait in memory in register order
+            // while the second block is multiplied; every lane reads back what it wrote itself (8192 x (2 x 4096) x 8192: 998 -> 921 us).
+#pragma clang fp contract(off)
+            char *tb = (char *)uniform_ptr((const char *)(p.carry + cur.slab_tile * (TM * TN) + wave_u * (RT * NT * 1024)));
+            const uint32_t lo = (uint32_t)elane * 16;
+            // (one sequence for both blocks: under a branch each, 380 registers went through scratch memory)
+            carried = cur.agg == 0;
+            f32x4 had[2][4];
+            auto fetch = [&](int q, f32x4 (&v)[4]) {
+#pragma unroll
+                for (int g = 0; g < 4; g++) v[g] = carried ? f32x4{-0.f, -0.f, -0.f, -0.f} : __builtin_nontemporal_load((const f32x4 *)(tb + (q * 4 + g) * 1024 + lo));
+            };
+            fetch(0, had[0]);
+#pragma unroll
+            for (int q = 0; q < RT * NT; q++) {
+                if (q + 1 < RT * NT) fetch(q + 1, had[(q + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < 16; r++) {
+                    const float s = p.alpha * own[q / NT][q % NT][r];
+                    own[q / NT][q % NT][r] = had[q & 1][r >> 2][r & 3] + s;
+                }
+                if (carried) {
+#pragma unroll
+                    for (int g = 0; g < 4; g++) {
+                        const f32x16 &o = own[q / NT][q % NT];
+                        const f32x4 val = {o[4 * g], o[4 * g + 1], o[4 * g + 2], o[4 * g + 3]};
+                        __builtin_nontemporal_store(val, (f32x4 *)(tb + (q * 4 + g) * 1024 + lo));
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (carried) {
+        } else if (KG == 1 && !CARRY && p.tile_order) {
             // Partial slabs in tile order (the launcher set this only for whole tiles): every accumulator register group goes out
             // as it is, 16 bytes per lane and 1 KiB per instruction, no staging; the aggregation kernel undoes the layout.
             float *tb = (float *)zb + cur.slab_tile * (TM * TN) + (int64_t)wave_u * (RT * NT * 4 * 64 * 4);
@@ -842,30 +892,30 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
 #undef EG_PIN
 }
 
-template <int TM, int TN, int KB, int NS, int WM, int NW, bool A_KC, bool B_KC, int REM, bool F32, bool TOT>
+template <int TM, int TN, int KB, int NS, int WM, int NW, bool A_KC, bool B_KC, int REM, bool F32, int MODE>
 static int launch_one(ContractParams &p, void *stream)
 {
-    EG_LAUNCH((k_contract_dma<TM, TN, KB, NS, WM, NW, A_KC, B_KC, REM, F32, TOT>), dim3((unsigned)p.grid), dim3(NW * 64), 0, (hipStream_t)stream, p);
+    EG_LAUNCH((k_contract_dma<TM, TN, KB, NS, WM, NW, A_KC, B_KC, REM, F32, MODE>), dim3((unsigned)p.grid), dim3(NW * 64), 0, (hipStream_t)stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(EG_ERR_HIP, "k_contract_dma launch failed: %s", hipGetErrorString(e));
     return EG_OK;
 }
 
-template <int TM, int TN, int KB, int NS, int WM, int NW, bool A_KC, bool B_KC, bool F32, bool TOT>
+template <int TM, int TN, int KB, int NS, int WM, int NW, bool A_KC, bool B_KC, bool F32, int MODE>
 static int launch_rem(ContractParams &p, void *stream)
 {
-    const int rem = (int)((TOT ? (int64_t)p.k_stages * p.n_totals : p.k_stages) % NS);
-    if (NS == 4 || rem == 0) return launch_one<TM, TN, KB, NS, WM, NW, A_KC, B_KC, 0, F32, TOT>(p, stream);
-    if constexpr (NS < 4) if (rem == 1) return launch_one<TM, TN, KB, NS, WM, NW, A_KC, B_KC, 1, F32, TOT>(p, stream);
-    if constexpr (NS == 3) if (rem == 2) return launch_one<TM, TN, KB, NS, WM, NW, A_KC, B_KC, 2, F32, TOT>(p, stream);
+    const int rem = (int)((MODE == 1 ? (int64_t)p.k_stages * p.n_totals : p.k_stages) % NS);
+    if (NS == 4 || rem == 0) return launch_one<TM, TN, KB, NS, WM, NW, A_KC, B_KC, 0, F32, MODE>(p, stream);
+    if constexpr (NS < 4) if (rem == 1) return launch_one<TM, TN, KB, NS, WM, NW, A_KC, B_KC, 1, F32, MODE>(p, stream);
+    if constexpr (NS == 3) if (rem == 2) return launch_one<TM, TN, KB, NS, WM, NW, A_KC, B_KC, 2, F32, MODE>(p, stream);
     return fail(EG_ERR_LIMIT, "k_contract_dma: stage count");
 }
 
-template <int TM, int TN, int KB, int NS, int WM, int NW, bool F32, bool TOT = false>
+template <int TM, int TN, int KB, int NS, int WM, int NW, bool F32, int MODE = 0>
 static int launch_layout(ContractParams &p, void *stream)
 {
-    if (p.a_kcontig) return p.b_kcontig ? launch_rem<TM, TN, KB, NS, WM, NW, true, true, F32, TOT>(p, stream) : launch_rem<TM, TN, KB, NS, WM, NW, true, false, F32, TOT>(p, stream);
-    return p.b_kcontig ? launch_rem<TM, TN, KB, NS, WM, NW, false, true, F32, TOT>(p, stream) : launch_rem<TM, TN, KB, NS, WM, NW, false, false, F32, TOT>(p, stream);
+    if (p.a_kcontig) return p.b_kcontig ? launch_rem<TM, TN, KB, NS, WM, NW, true, true, F32, MODE>(p, stream) : launch_rem<TM, TN, KB, NS, WM, NW, true, false, F32, MODE>(p, stream);
+    return p.b_kcontig ? launch_rem<TM, TN, KB, NS, WM, NW, false, true, F32, MODE>(p, stream) : launch_rem<TM, TN, KB, NS, WM, NW, false, false, F32, MODE>(p, stream);
 }
 
 // one per unit of instantiations; each returns eg_status
@@ -873,6 +923,7 @@ int launch_256(ContractParams &p, int nw, void *stream);              // 256 x 2
 int launch_256x128(ContractParams &p, void *stream);
 int launch_128(ContractParams &p, int ns, void *stream);              // 128 x 128, two or four stages
 int launch_totals(ContractParams &p, int ns, void *stream);           // ... which keeps the totals of n_totals blocks
+int launch_carry(ContractParams &p, void *stream);                     // 256 x 256, two blocks, the first one's sums wait in memory
 
 }  // namespace dma
 

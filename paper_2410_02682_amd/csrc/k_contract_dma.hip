@@ -78,7 +78,8 @@ void contract_dma_variant(const ContractParams &p, int &tm, int &tn, int &nw, in
     auto count = [&](int tm, int tn) { return tuples * ((p.M + tm - 1) / tm) * ((p.N + tn - 1) / tn); };
     const int64_t small = count(128, 128);
     const int64_t ntail = p.N % 256;
-    if (small <= 2 * n_cu || p.n_totals > 1) tm = tn = 128;
+    if (p.carry) tm = tn = 256;
+    else if (small <= 2 * n_cu || p.n_totals > 1) tm = tn = 128;
     else if (!f32 && (p.K <= 128 || (ntail > 0 && ntail <= 128 && p.N < 1024))) { tm = 256; tn = 128; }
     else if (4 * count(256, 256) * 10 > small * 14) tm = tn = 128;
     else tm = tn = 256;
@@ -127,6 +128,26 @@ bool contract_totals_pay(const ContractParams &p, int64_t n_agg, int out_bytes)
     return totals < join + 5 + bytes / 5.3e6;
 }
 
+// Two blocks of long reductions on whole 256 x 256 tiles: a workgroup multiplies a tile's blocks one after the other and the first
+// one's sums wait for the second's in the first slab.  Saves the other slab's way through memory and the aggregation, for a read
+// (some 12 us per tile) that nothing covers.  us, two blocks of K (slabs and aggregation / totals in registers / this):
+//   4096 x 4096    K = 1024 109 / 75 / 86      2048 155 / 134 / 132    4096 248 / 254 / 226
+//   8192 x 4096    K = 1024 197 / 141 / 155    2048 291 / 264 / 246    4096 481 / 495 / 439
+//   16384 x 4096   K = 1024 372 / 280 / 283    2048 569 / 522 / 486    4096 973 / 1026 / 937
+//   5120 x 4096    K = 4096 333 / 310 / 373    (a second round of 64 tiles, twice as long: whole rounds only)
+// Four blocks, whose totals are read and written in between: 491 / 527 / 478 at 4096 x 4096 of K = 4096, 1122 / 1046 / 1132 at 16384 x
+// 4096 of 2048; left to the others.
+bool contract_carry_pays(const ContractParams &p, int64_t n_agg)
+{
+    const int n_cu = dma_cu_count();
+    if (!n_cu || n_agg != 2 || p.n_tuples % 2 || p.in_dtype == EG_F32 || p.M % 256 || p.N % 256 || p.K < 2048) return false;
+    if (p.force_tile_m || p.force_tile_n || p.force_waves == 4) return false;
+    int tm, tn, nw, ns;
+    contract_dma_variant(p, tm, tn, nw, ns);
+    if (tm != 256 || tn != 256) return false;
+    const int64_t tiles = p.n_tuples / 2 * p.n_batch * (p.M / 256) * (p.N / 256);
+    return 2 * tiles < (1ll << 31) && 2 * ((tiles + n_cu - 1) / n_cu) <= (2 * tiles + n_cu - 1) / n_cu;
+}
 
 int launch_contract_dma(ContractParams &p, void *stream)
 {
@@ -139,7 +160,8 @@ int launch_contract_dma(ContractParams &p, void *stream)
     int tm, tn, nw, ns;
     contract_dma_variant(p, tm, tn, nw, ns);
     if (p.tile_order && ns == 4) return fail(EG_ERR_LIMIT, "contraction: the four-stage kernel has no tile order");
-    if (p.n_totals > 1 && (tm != 128 || tn != 128 || p.out.slab_elems)) return fail(EG_ERR_LIMIT, "contraction: totals are kept by 128 x 128 tiles, in place of partial slabs");
+    if (p.carry && (tm != 256 || tn != 256 || nw != 8 || f32 || p.n_totals != 2 || p.out.slab_elems || p.tile_order || p.M % 256 || p.N % 256)) return fail(EG_ERR_LIMIT, "contraction: sums wait in memory for those of a second block, whole 256 x 256 tiles of bf16 operands");
+    if (!p.carry && p.n_totals > 1 && (tm != 128 || tn != 128 || p.out.slab_elems)) return fail(EG_ERR_LIMIT, "contraction: totals are kept by 128 x 128 tiles, in place of partial slabs");
     if (p.tile_order && (p.M % tm || p.N % tn || !p.out.slab_elems)) return fail(EG_ERR_LIMIT, "contraction: tile-ordered partial slabs need whole tiles");
     // the variant: stage depth and waves follow from the tile shape
     const int kb = (tm == 256 && tn == 128) ? 64 : 128;
@@ -202,6 +224,7 @@ int launch_contract_dma(ContractParams &p, void *stream)
             }
         }
     }
+    if (p.carry) return wgs * p.n_totals < (1ll << 31) ? dma::launch_carry(p, stream) : fail(EG_ERR_LIMIT, "contraction has too many tiles");
     if (p.n_totals > 1) return dma::launch_totals(p, ns, stream);
     if (tm == 128) return dma::launch_128(p, ns, stream);
     if (tn == 128) return dma::launch_256x128(p, stream);
