@@ -31,19 +31,11 @@ DEFAULT_PART = {1: "d222", 2: "mix", 3: "batch8", 4: "heads8", 5: "k16", 6: "spl
 # file, scaled by what the same counters read for the plain 1 GiB copy kernel (see profiles/); a family that is not listed
 # reports null.  Keys: (workload, partitioning, kernel family).
 MEASURED_TRAFFIC = {
-    ("c2", "mix", "contract_mfma"): 2189732864,    # 1575 MiB fetched + 513 MiB written per launch (1575-1690 MiB fetched over the pool's boxes)
-    ("c2", "mix", "aggregate"): 739217408,         # 512 MiB fetched + 193 MiB written
-    ("c3", "batch8", "contract_mfma"): 481092000,  # 212 MiB fetched + 247 MiB written (mean over the step's five contractions)
     ("c3", "batch8", "map"): 83944448,             # 48 MiB fetched + 32 MiB written (mean over the ReLU and its gradient; the other maps run inside the softmax pass)
     ("c3", "batch8", "softmax_fused"): 51062784,   # 24.7 MiB fetched (logits and labels) + 24 MiB written (log-probabilities and the gradient dL)
     ("c3", "batch8", "reduce_row"): 25293930,      # 24 MiB fetched
-    ("c3", "batch8", "aggregate"): 453230000,      # 384 MiB fetched + 48 MiB written (mean over the step's three aggregations)
-    ("c4", "heads8", "contract_mfma"): 1280241700, # 812 MiB fetched + 409 MiB written (mean over the step's nine contractions)
     ("c4", "heads8", "softmax_fused"): 2281005450, # 1152 MiB fetched (scores + the mask rows) + 1023 MiB written
-    ("c4", "heads8", "aggregate"): 1174699000,     # 1024 MiB fetched + 96 MiB written
     ("c4", "heads8", "map"): 549389600,            # 352 MiB fetched + 172 MiB written
-    ("c5", "k16", "contract_mfma"): 31395302400,   # 13556 MiB fetched (L2 misses; the re-reads of X are served by the Infinity Cache) + 16385 MiB written
-    ("c5", "k16", "aggregate"): 18253883392,       # 16384 MiB fetched + 1024 MiB written
 }
 
 
