@@ -1685,7 +1685,8 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
                 rt.cp.n_tuples /= s.slabs;
                 rt.cp.force_kernel = s.r.cp.force_kernel;
                 rt.cp.force_waves = s.r.cp.force_waves;
-                if (rt.ragged ? contract_ragged_totals_pay(s.r.cp, s.slabs, (int)dtype_size(v.dtype)) : contract_takes_dma(rt.cp)) {
+                // (the result's own strides may keep labels from joining that join in a dense slab: no totals on the form such products take)
+                if (rt.ragged ? contract_ragged_streams(rt.cp) : contract_takes_dma(rt.cp)) {
                     s.r = rt;
                     s.agg = false;
                 }

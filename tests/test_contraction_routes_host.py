@@ -1,4 +1,5 @@
-"""Which kernel a cut contraction runs on and how much workspace it takes (host code, no GPU needed)."""
+"""Which kernel a cut contraction runs on, how much workspace it takes and which calls are accepted (host code, no GPU needed)."""
+import ctypes
 import math
 
 import pytest
@@ -82,3 +83,43 @@ def test_ragged_products_take_tiles_where_these_fill_the_chip(spec, bx, by, dt, 
 def test_ragged_scalar_functions_with_tiles(otimes, oplus, kernel):
     """Operators read at run time take ten times as long on a tile, so only the compiled pairs have ragged tiles."""
     assert vertex("ij,jk->ik", (1025, 63), (63, 2051), {}, dt="f32", otimes=otimes, oplus=oplus)[0] == kernel
+
+
+def refusal(spec, bx, by, cut, dt, out, zstrides=None):
+    """What tr_execute answers to one vertex before it launches anything.  Every launcher makes its checks first, so without a GPU
+    the error is that of the missing device, or an earlier refusal; the operands' addresses are never touched."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("stops at the missing device")
+    room = ctypes.create_string_buffer(512)
+    at = (ctypes.addressof(room) + 255) // 256 * 256
+    g, rels = E.einsum_graph_create(), []
+    try:
+        x, y = E.einsum_graph_add_input(g, list(bx), dt), E.einsum_graph_add_input(g, list(by), dt)
+        z = E.einsum_graph_add_einsum(g, spec, "mul", "sum", 1.0, [x, y], out)
+        names = spec.split("->")[0].replace(",", "")
+        E.einsum_graph_set_partition(g, z, [cut.get(l, 1) for l in dict.fromkeys(names)])
+        E.einsum_graph_mark_output(g, z)
+        ext = dict(zip(names, tuple(bx) + tuple(by)))
+        bz = [ext[l] for l in spec.split("->")[1]]
+        for b, t, st in ((bx, dt, None), (by, dt, None), (bz, out, zstrides)):
+            rels.append(E.tensor_partition(at, t, list(b), [1] * len(b), st))
+        with pytest.raises(E.EgError) as e:
+            E.tr_execute(g, rels[:2], rels[2:], at, 1 << 50)
+        return str(e.value)
+    finally:
+        for r in rels:
+            E.tensor_relation_destroy(r)
+        E.einsum_graph_destroy(g)
+
+
+@pytest.mark.parametrize("dt,out", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32")])
+@pytest.mark.parametrize("spec,bx,by,cut,zstrides", [
+    ("jab,jk->abk", (130, 13, 79), (130, 1101), {"j": 2}, [82 * 1101, 1101, 1]),          # row labels that do not join in the result
+    ("jab,jk->abk", (1000, 30, 35), (1000, 1101), {"j": 8}, [40 * 1101, 1101, 1]),
+    ("ij,jab->iab", (1101, 130), (130, 13, 79), {"j": 2}, [13 * 82, 82, 1]),              # column labels
+    ("bf,bhd->fhd", (1000, 3001), (1000, 5, 77), {"b": 8}, [400, 80, 1]),
+])
+def test_ragged_cut_products_into_strided_results_are_accepted(spec, bx, by, cut, zstrides, dt, out):
+    for z in (None, zstrides):
+        assert "no ROCm-capable device" in refusal(spec, bx, by, cut, dt, out, z)

@@ -16,7 +16,7 @@ TYPES = [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32")]
 SIZES = [(65, 63, 17), (77, 129, 33), (9, 513, 63), (130, 67, 65), (64, 67, 97), (201, 73, 127), (67, 64, 129), (71, 61, 257), (65, 129, 515)]
 
 
-def _run(w, x, y, pad=False, tiled=None):
+def _run(w, x, y, pad=False, tiled=None, out=None):
     import torch
     import paper_2410_02682_amd as E
     from paper_2410_02682_amd.runner import GraphRunner, to_device, to_host
@@ -32,7 +32,7 @@ def _run(w, x, y, pad=False, tiled=None):
 
     r = GraphRunner(w, "d", tiled_partials=tiled)
     try:
-        r.bind({"X": bound(x), "Y": bound(y)})
+        r.bind({"X": bound(x), "Y": bound(y)}, outputs=None if out is None else {"Z": out})
         kernel = r.plan("Z")["kernel"]
         E.tr_profile_enable(r.g, 8)
         r.run()
@@ -74,3 +74,25 @@ def test_blocks_along_the_contracted_label(spec, bx, by, part, dt, odt):
         assert kernel == "contract_mfma" and launches == stages, (kernel, launches)
         bad, worst = violations(got, ref, RTOL_BF16 if odt == "bf16" else RTOL_F32)
         assert bad == 0, f"tiled {tiled}: {bad} elements out of tolerance (worst {worst:.2f}x)"
+
+
+@pytest.mark.parametrize("dt,odt", TYPES)
+@pytest.mark.parametrize("spec,bx,by,pad,joins", [
+    ("ij,jk->ik", (517, 2 * 65), (2 * 65, 643), (0, 21), True),
+    ("jab,jk->abk", (2 * 65, 13, 39), (2 * 65, 643), (0, 3, 0), False),        # row labels that join in a dense result only
+    ("ij,jab->iab", (517, 2 * 65), (2 * 65, 13, 49), (0, 0, 3), False),        # column labels
+])
+def test_blocks_into_a_strided_result(spec, bx, by, pad, joins, dt, odt):
+    import torch
+    print(f"ragged blocks into a strided result {spec} X{bx} Y{by} {dt}->{odt}", flush=True)
+    x, y = (HostTensor.from_f32(uniform_pm1(73, p, int(np.prod(b))).reshape(b), dt) for p, b in enumerate((bx, by)))
+    w = single_vertex(spec, x, y, odt, parts={"d": {"j": 2}})
+    ref = run_graph(w, {"X": x, "Y": y})["Z"].as_f64()
+    big = torch.full([n + p for n, p in zip(ref.shape, pad)], 7.0, dtype=torch.float32 if odt == "f32" else torch.bfloat16, device="cuda")
+    view = big[tuple(slice(0, n) for n in ref.shape)]
+    got, kernel, launches = _run(w, x, y, out=view)
+    assert kernel == "contract_mfma" and launches == (["join"] if joins else ["join", "aggregate"]), (kernel, launches)
+    bad, worst = violations(got, ref, RTOL_BF16 if odt == "bf16" else RTOL_F32)
+    assert bad == 0, f"{bad} elements out of tolerance (worst {worst:.2f}x)"
+    view.fill_(7.0)
+    assert bool((big == 7.0).all())
