@@ -1639,7 +1639,7 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
                 const int64_t room = L.partial_off[i] >= 0 ? v.plan.n_agg * L.split[i] : 1;
                 const int pieces = contract_rows_pieces(rt.cp, room);
                 const OutSpec slabs{pieces > 1 ? ws + L.partial_off[i] : nullptr, slab_stride_of(numel(v.bound), pieces), EG_F32};
-                bool ok = true;
+                bool ok = pieces > 0;
                 if (pieces > 1) {
                     rt = Routed();
                     ok = route(v1, X, &Y, dense_strides(v.bound), slabs, rt, 1) == EG_OK && rt.kind == EG_KERNEL_CONTRACT_MFMA && !rt.ragged && contract_rows_suits(rt.cp);

@@ -175,19 +175,21 @@ bool contract_rows_suits(const ContractParams &p)
 }
 
 // How many pieces the contracted label is cut into, of at most `slabs`, so that every compute unit has a workgroup; and so many that
-// no wave sums up more of it than a slab's block does
+// no wave sums up more of it than a slab's block does.  0: more than a grid has room for, not for this kernel
+constexpr int kMaxPieces = 65535;
 int contract_rows_pieces(const ContractParams &p, int64_t slabs)
 {
     const int64_t groups = p.b_kcontig ? (p.N + 15) / 16 : (p.N + 63) / 64;
     int64_t s = groups >= 160 ? 1 : (256 + groups - 1) / groups;         // (8 x 4096 x 11008: 23.1 us in one piece, 22.4 to 26.4 in 2 to 8 and their aggregation)
     s = std::min(s, std::min(slabs, p.K / 256));
-    return (int)std::max<int64_t>(s, (slabs + rows::kWaves - 1) / rows::kWaves);
+    s = std::max<int64_t>(s, (slabs + rows::kWaves - 1) / rows::kWaves);
+    return s <= kMaxPieces ? (int)s : 0;
 }
 
 int launch_contract_rows(ContractParams &p, int pieces, void *stream)
 {
     if (!p.x || !p.y || !p.out.ptr) return fail(EG_ERR_NULL, "contraction: NULL operand");
-    if (!contract_rows_suits(p) || pieces < 1 || pieces > 65535 || (pieces > 1) != (p.out.slab_elems != 0)) return fail(EG_ERR_LIMIT, "contraction: shape not eligible for the few-row kernel");
+    if (!contract_rows_suits(p) || pieces < 1 || pieces > kMaxPieces || (pieces > 1) != (p.out.slab_elems != 0)) return fail(EG_ERR_LIMIT, "contraction: shape not eligible for the few-row kernel");
     p.k_stages = (int32_t)(((p.K + pieces - 1) / pieces + 31) / 32 * 32);
     // columns per lane: 8, or 4 where that gives too few workgroups
     const bool wide = (p.N + 127) / 128 * pieces >= 256;

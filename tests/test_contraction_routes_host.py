@@ -87,7 +87,7 @@ def test_ragged_scalar_functions_with_tiles(otimes, oplus, kernel):
 
 def refusal(spec, bx, by, cut, dt, out, zstrides=None):
     """What tr_execute answers to one vertex before it launches anything.  Every launcher makes its checks first, so without a GPU
-    the error is that of the missing device, or an earlier refusal; the operands' addresses are never touched."""
+    the error is that of the missing device (EG_ERR_HIP), or an earlier refusal; the operands' addresses are never touched."""
     import torch
     if torch.cuda.is_available():
         pytest.skip("stops at the missing device")
@@ -122,4 +122,11 @@ def refusal(spec, bx, by, cut, dt, out, zstrides=None):
 ])
 def test_ragged_cut_products_into_strided_results_are_accepted(spec, bx, by, cut, zstrides, dt, out):
     for z in (None, zstrides):
-        assert "no ROCm-capable device" in refusal(spec, bx, by, cut, dt, out, z)
+        assert "error -12:" in refusal(spec, bx, by, cut, dt, out, z)
+
+
+@pytest.mark.parametrize("rows", [2, 16])
+@pytest.mark.parametrize("cut", [262144, 524280, 524288, 600000])
+def test_few_rows_cut_into_more_blocks_than_a_grid_has_pieces(rows, cut):
+    """Eight blocks a piece at most, 65535 pieces a launch: beyond 524280 blocks the vertex stays on the tiles."""
+    assert "error -12:" in refusal("ij,jk->ik", (rows, 8 * cut), (8 * cut, 64), {"j": cut}, "bf16", "f32")
