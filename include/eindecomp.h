@@ -255,7 +255,10 @@ int tr_set_fused_aggregation(eg_graph *g, int enable);
  * bit for bit.  And where that is estimated to be faster, the kernel walks over the blocks that share an output block and
  * adds their sums itself, in the same order, each scaled and rounded as its slab would hold it: nothing is written in
  * between and no aggregation launch follows (the results are the same bit for bit, or, where the kernel splits a tile's
- * reduction over two groups of waves, sums of the same terms in another order).  enable = 0: every slab is the dense
+ * reduction over two groups of waves, sums of the same terms in another order; ragged products, whose totals are kept in 64
+ * bits, are rounded once instead of once per block).  A product of at most 16 rows with a large matrix is cut along its
+ * contracted labels into pieces of the library's choice instead of the vertex's own blocks, at most as many, and these are
+ * aggregated: the same terms in another order.  enable = 0: every block of the vertex has a slab, every slab is the dense
  * row-major tensor (what tr_aggregate takes) and is aggregated.  For comparisons and tests.  Takes effect at the next
  * tr_execute. */
 int tr_set_tiled_partials(eg_graph *g, int enable);
@@ -282,7 +285,8 @@ int tr_set_fused_attention(eg_graph *g, int enable);
  * the same up to summation order.  kernel: 0 = the library chooses per vertex, 1 = the register-staged kernel,
  * 2 = the direct-to-LDS kernel wherever the operand layout allows it.  tile_m x tile_n: 0 x 0 = the library chooses;
  * 128 x 128, 256 x 128 or 256 x 256 = output tile of the direct-to-LDS kernel (fp32 operands have no 256 x 128 variant
- * and take 256 x 256 instead).  waves: 0 = the library chooses, 4 or 8 = waves per workgroup of the 256 x 256 variant.
+ * and take 256 x 256 instead).  waves: 0 = the library chooses, 4 or 8 = waves per workgroup of the 256 x 256 variant; 4 also
+ * keeps 128 x 128 tiles on four waves, where the library takes eight and more stages in LDS for a launch of few tiles.
  * Other values: EG_ERR_LIMIT.  Takes effect at the next tr_execute; changes no workspace size. */
 int tr_set_contract_variant(eg_graph *g, int kernel, int tile_m, int tile_n, int waves);
 

@@ -1630,8 +1630,9 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
             s.r.cp.force_waves = g->contract_waves;
         }
         // Few rows times a large matrix: a kernel that streams the matrix, cut along the contracted label into no more pieces than the
-        // vertex has slabs in the workspace.
-        if (!merged && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && s.r.cp.M <= 16 && !s.r.cp.force_kernel && !s.r.cp.force_tile_m && !s.r.cp.force_waves) {
+        // vertex has slabs in the workspace.  The pieces take the place of the vertex's own blocks, which tr_set_tiled_partials(g, 0)
+        // asks to see.
+        if (!merged && (g->tiled_partials || v.plan.n_agg == 1) && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && s.r.cp.M <= 16 && !s.r.cp.force_kernel && !s.r.cp.force_tile_m && !s.r.cp.force_waves) {
             const Vertex v1 = single_vertex(v);
             Routed rt;
             const OutSpec direct{s.dst, 0, (int32_t)v.dtype};
