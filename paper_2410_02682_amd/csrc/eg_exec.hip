@@ -43,6 +43,17 @@ static int64_t numel(const std::vector<int64_t> &bound)
     return n;
 }
 
+// May the two tensors share memory?  (By the ranges they span: interleaved views of one buffer count as shared.)
+static bool may_overlap(const Operand &a, const std::vector<int64_t> &abound, const Operand &b, const std::vector<int64_t> &bbound)
+{
+    auto end = [](const Operand &o, const std::vector<int64_t> &bound) {          // (strides are not negative)
+        int64_t last = 0;
+        for (size_t i = 0; i < bound.size(); i++) last += (bound[i] - 1) * o.stride[i];
+        return (uintptr_t)o.ptr + (uintptr_t)((last + 1) * dtype_size(o.dtype));
+    };
+    return (uintptr_t)a.ptr < end(b, bbound) && (uintptr_t)b.ptr < end(a, abound);
+}
+
 // Per schema label: stride in each operand (0 when the label is absent), block extent.
 struct LabelInfo {
     int nl = 0;
@@ -1629,10 +1640,12 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
             s.r.cp.force_tile_n = g->contract_tile_n;
             s.r.cp.force_waves = g->contract_waves;
         }
+        // A result bound over one of its own operands is written only when all of that has been read: through slabs.
+        const bool in_place = s.agg && v.n_in == 2 && (may_overlap(Z, v.bound, X, g->v[v.in[0]].bound) || may_overlap(Z, v.bound, Y, g->v[v.in[1]].bound));
         // Few rows times a large matrix: a kernel that streams the matrix, cut along the contracted label into no more pieces than the
         // vertex has slabs in the workspace.  The pieces take the place of the vertex's own blocks, which tr_set_tiled_partials(g, 0)
         // asks to see.
-        if (!merged && (g->tiled_partials || v.plan.n_agg == 1) && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && s.r.cp.M <= 16 && !s.r.cp.force_kernel && !s.r.cp.force_tile_m && !s.r.cp.force_waves) {
+        if (!merged && !in_place && (g->tiled_partials || v.plan.n_agg == 1) && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && s.r.cp.M <= 16 && !s.r.cp.force_kernel && !s.r.cp.force_tile_m && !s.r.cp.force_waves) {
             const Vertex v1 = single_vertex(v);
             Routed rt;
             const OutSpec direct{s.dst, 0, (int32_t)v.dtype};
@@ -1658,7 +1671,7 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
             }
         }
         // Two long blocks: a tile's sums wait in the first slab while its second block is multiplied; no aggregation.
-        if (s.agg && !refined && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && s.partials && contract_takes_dma(s.r.cp) &&
+        if (s.agg && !refined && !in_place && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA && !s.r.ragged && s.partials && contract_takes_dma(s.r.cp) &&
             contract_carry_pays(s.r.cp, s.slabs)) {
             const OutSpec direct{s.dst, 0, (int32_t)v.dtype};
             Routed rt;
@@ -1676,7 +1689,7 @@ static int execute_graph(eg_graph *g, eg_relation *const *inputs, int n_inputs, 
         }
         // Blocks along aggregated labels whose sums the kernel can total itself, where that is faster: no slabs, no aggregation.  (The
         // slabs stay in the workspace's layout, which does not know the strides and addresses that relations are bound with.)
-        if (s.agg && !refined && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA &&
+        if (s.agg && !refined && !in_place && g->tiled_partials && s.r.kind == EG_KERNEL_CONTRACT_MFMA &&
             (s.r.ragged ? contract_ragged_totals_pay(s.r.cp, s.slabs, (int)dtype_size(v.dtype))
                         : contract_takes_dma(s.r.cp) && contract_totals_pay(s.r.cp, s.slabs, (int)dtype_size(v.dtype)))) {
             const OutSpec direct{s.dst, 0, (int32_t)v.dtype};
