@@ -283,7 +283,8 @@ int tr_set_fused_attention(eg_graph *g, int enable);
 /* Which variant of the block-contraction kernel the (x) = multiply, (+) = sum vertices of this graph run on, for
  * comparisons and for tests that must reach every variant at sizes the library would route elsewhere; results are
  * the same up to summation order.  kernel: 0 = the library chooses per vertex, 1 = the register-staged kernel,
- * 2 = the direct-to-LDS kernel wherever the operand layout allows it.  tile_m x tile_n: 0 x 0 = the library chooses;
+ * 2 = the direct-to-LDS kernel wherever the operand layout allows it, with blocks along aggregated labels totalled in the
+ * kernel from 32 output tiles on (unless a tile is named or tr_set_tiled_partials is off).  tile_m x tile_n: 0 x 0 = the library chooses;
  * 128 x 128, 256 x 128 or 256 x 256 = output tile of the direct-to-LDS kernel (fp32 operands have no 256 x 128 variant
  * and take 256 x 256 instead).  waves: 0 = the library chooses, 4 or 8 = waves per workgroup of the 256 x 256 variant; 4 also
  * keeps 128 x 128 tiles on four waves, where the library takes eight and more stages in LDS for a launch of few tiles.

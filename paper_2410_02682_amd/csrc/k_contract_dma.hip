@@ -109,6 +109,11 @@ void contract_dma_variant(const ContractParams &p, int &tm, int &tn, int &nw, in
 //   512 x (2 x 1840) x 1536 to bf16                              34.4        38.3
 //   1024 x (8 x 12800) x 10240 to bf16                     1860 + 56          -      (160 large tiles: the pieces fill the chip)
 // Under 32 tiles the blocks' own workgroups are worth more than the launch that is saved (unless the reduction is a few stages long).
+// While the totals' tiles fit the compute units once, both ways are estimated to a few percent instead, with what a block costs that is
+// walked over (its offsets, the folding of its sums) and what an aggregation does for small slabs: 420 shapes of 16 to 1536
+// elements a block and 140 of 1024 to 8192, each on both ways; the way taken is 0.2 % slower than the better one on average and nowhere more
+// than 4 % slower than slabs, apart from two shapes (11 and 6 %).  (2632 x (16 x 128) x 144 to fp32: slabs 22.8 us, totals 32.0; 4608 x
+// (3 x 1536) x 952 29.9 and 39.5; 696 x (4 x 320) x 648 13.8 and 17.7; 1072 x (16 x 128) x 2968 85 and 37.)
 bool contract_totals_pay(const ContractParams &p, int64_t n_agg, int out_bytes)
 {
     const int n_cu = dma_cu_count();
@@ -120,10 +125,25 @@ bool contract_totals_pay(const ContractParams &p, int64_t n_agg, int out_bytes)
     auto rounds = [](int64_t tiles, int64_t wgs) { return (double)((tiles + wgs - 1) / wgs); };
     const int64_t small = count(128), large = count(256);
     if (small < 32 || small * n_agg >= (1ll << 31)) return false;
+    if (p.force_kernel == 2) return true;                                  // asked for by name: this form of the kernel at any such size
     const double n = (double)n_agg, stages = (double)((p.K * (f32 ? 4 : 2) + 127) / 128);
-    const double one = f32 ? 2.1 : 0.65, two = f32 ? 4.1 : 1.0, big = f32 ? 8.0 : 1.5;      // us per stage: a 128 x 128 tile alone, two, a 256 x 256 tile
-    const double totals = small <= n_cu ? (f32 ? one : 0.45) * stages * n : rounds(small, 2 * n_cu) * (two * stages * n + 2.5);
-    const double join = small * n_agg <= n_cu ? one * stages : small * n_agg <= 2 * n_cu ? two * stages : rounds(large * n_agg, n_cu) * (big * stages + 2.5);
+    if (small <= n_cu) {
+        const double mb = (double)outs * p.M * p.N * (4 * n + out_bytes) * 1e-6;
+        const double totals = f32 ? 8 + n * (2.1 * stages + 0.6) : p.K * n_agg >= 512 ? 7.2 + n * (0.42 * stages + 0.8) : 6 + n * (0.52 * stages + 0.65);
+        int tm, tn, nw, ns;
+        contract_dma_variant(p, tm, tn, nw, ns);                          // the blocks' own tiles
+        const int64_t tiles = outs * n_agg * ((p.M + tm - 1) / tm) * ((p.N + tn - 1) / tn);
+        double slabs;
+        if (tm == 256 && tn == 256) slabs = f32 ? 13.4 + rounds(tiles, n_cu) * (2.7 + 6.5 * stages) + 0.23 * mb + 0.15 * n : 9.1 + rounds(tiles, n_cu) * (2.85 + 1.06 * stages) + 0.28 * mb;
+        else if (tm == 256) slabs = 12.9 + rounds(tiles, 2 * n_cu) * (0.23 + 1.07 * stages) + 0.234 * mb + 0.17 * n;
+        else if (tiles <= n_cu) slabs = (f32 ? 8 + 2.1 * stages : 6.6 + 0.525 * stages) + 0.44 * mb + 0.3 * n;
+        else if (tiles <= 2 * n_cu) slabs = f32 ? 7.9 + 3.4 * stages + 0.37 * mb + 0.6 * n : 9.9 + 0.57 * stages + 0.32 * mb + 0.23 * n;
+        else slabs = 9.9 + rounds(tiles, 2 * n_cu) * (1.5 + (f32 ? 4.1 : 1.0) * stages) + 0.28 * mb;
+        return totals < slabs;
+    }
+    const double two = f32 ? 4.1 : 1.0, big = f32 ? 8.0 : 1.5;                              // us per stage: two 128 x 128 tiles, a 256 x 256 tile
+    const double totals = rounds(small, 2 * n_cu) * (two * stages * n + 2.5);
+    const double join = small * n_agg <= 2 * n_cu ? two * stages : rounds(large * n_agg, n_cu) * (big * stages + 2.5);
     const double bytes = (double)outs * p.M * p.N * (4 * n + out_bytes);
     return totals < join + 5 + bytes / 5.3e6;
 }

@@ -100,3 +100,33 @@ def test_totals_into_a_strided_destination():
         assert bool((big == 7.0).all())
         outs.append(z)
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("spec,bx,by,cut,out_dtype,totals", [
+    ("ij,jk->ik", (2632, 2048), (2048, 144), 16, "f32", False),              # 42 tiles: slabs 22.8 us, totals 32.0
+    ("ji,kj->ik", (4608, 1504), (952, 4608), 3, "bf16", False),              # 96 tiles: 29.9 and 39.5
+    ("ij,jk->ik", (696, 1280), (1280, 648), 4, "bf16", False),               # 36 tiles: 13.8 and 17.7
+    ("ij,jk->ik", (1072, 2048), (2048, 2968), 16, "bf16", True),             # 216 tiles: 85 and 37
+    ("ij,jk->ik", (2168, 512), (512, 728), 2, "bf16", True),                 # 102 tiles: 17.5 and 12.0
+])
+def test_totals_only_where_they_are_faster_than_slabs(spec, bx, by, cut, out_dtype, totals):
+    print(f"totals or slabs {spec} X{bx} Y{by} j cut {cut}", flush=True)
+    assert _stages(spec, bx, by, cut, "bf16", out_dtype) == (["join"] if totals else ["join", "aggregate"])
+
+
+def _stages(spec, bx, by, cut, in_dtype, out_dtype):
+    """The launches of one vertex as the library routes it; operands of zeros."""
+    import torch
+    import paper_2410_02682_amd as E
+    from paper_2410_02682_amd.runner import TORCH_DTYPE, GraphRunner
+    w = single_vertex(spec, HostTensor(np.zeros(bx, np.uint16 if in_dtype == "bf16" else np.float32), in_dtype),
+                      HostTensor(np.zeros(by, np.uint16 if in_dtype == "bf16" else np.float32), in_dtype), out_dtype, parts={"d": {"j": cut}})
+    r = GraphRunner(w, "d")
+    try:
+        r.bind({n: torch.zeros(b, dtype=TORCH_DTYPE[in_dtype], device="cuda") for n, b in (("X", bx), ("Y", by))})
+        E.tr_profile_enable(r.g, 8)
+        r.run()
+        torch.cuda.synchronize()
+        return [q["stage"] for q in E.tr_profile_read(r.g)]
+    finally:
+        r.close()
