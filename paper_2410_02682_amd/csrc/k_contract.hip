@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <type_traits>
@@ -772,16 +773,32 @@ bool contract_ragged_streams(const ContractParams &p)
     return (p.a_kcontig || (p.m.n == 1 && p.M >= epc)) && (p.b_kcontig || (p.n.n == 1 && p.N >= epc));
 }
 
-// Do they run faster with a tile's blocks one after another in one workgroup than each with its own, slabs and an aggregation?
-// A stage takes 2.5 us on the fp64 instruction (fp32 operands 1.4), 0.6 on the bf16 one.  (3001 x (8 x 125) x 1530 to fp32: 259 us and
-// 28 for the aggregation through slabs, 215 without; 1530 x (8 x 125) x 1003 98 and 12, 92.)
+// Do they run faster with a tile's blocks one after another in one workgroup than each with its own, slabs and an aggregation?  Both
+// ways in us, by rounds of 256 tiles (of two and three workgroups on a compute unit a round costs 0.8 to 0.9) and stages, with what a
+// block costs that is walked over, and the slabs' way through memory at some 1.6 TB/s (they are small); two launches take 10 us at the
+// least.  A stage of bf16 operands on the fp64 instruction may be cut short by half.  From 420 shapes of 17 to 2500 rows and columns
+// and blocks of 9 to 1500 elements, each on both ways: the way taken is 0.5 to 1.5 % slower than the better one on average and
+// at most 8 % slower than slabs.  (315 x (16 x 324) x 200 to bf16: slabs 16.9 us, totals 88.9; 1871 x (3 x 1335) x 706 bf16 to fp32
+// 259 and 300; 3001 x (8 x 125) x 1530 fp32 287 and 215; 2477 x (8 x 81) x 1273 to bf16 85 and 41.)
 bool contract_ragged_totals_pay(const ContractParams &p, int64_t n_agg, int out_bytes)
 {
     if (n_agg < 2 || n_agg > INT32_MAX || p.n_tuples % n_agg || !contract_ragged_streams(p)) return false;
+    const bool bf = p.in_dtype == EG_BF16;
     const double outs = (double)(p.n_tuples / n_agg * p.n_batch), tiles = outs * ((p.M + 63) / 64) * ((p.N + 63) / 64), n = (double)n_agg;
-    const int bk = p.in_dtype == EG_BF16 ? 64 : 32;
-    const double stages = (double)((p.K + bk - 1) / bk) * (!p.wide ? 0.6 : p.in_dtype == EG_BF16 ? 2.5 : 1.4);
-    return std::max(tiles / 256, 1.0) * stages * n < std::max(tiles * n / 256, 1.0) * (stages + 1) + 5 + outs * p.M * p.N * (4 * n + out_bytes) / 5.3e6;
+    const double mb = outs * p.M * p.N * (4 * n + out_bytes) * 1e-6, c = std::ceil(tiles / 256), w = std::ceil(tiles * n / 256);
+    const double stages = bf && p.wide ? (double)((p.K + 31) / 32) / 2 : (double)((p.K + (bf ? 63 : 31)) / (bf ? 64 : 32));
+    double totals, slabs;
+    if (!p.wide) {
+        totals = 6.1 + n * (0.62 * stages + 0.35) * std::max(1.0, 0.8 * c);
+        slabs = 8.0 + std::max(1.0, 0.8 * w) * (0.632 * stages - 0.469) + 0.611 * mb;
+    } else if (bf) {
+        totals = 6.0 + n * (2.4 * stages + 0.6) * c;
+        slabs = 6.9 + w * (2.58 * stages + 0.78) + 0.563 * mb;
+    } else {
+        totals = 7.2 + n * (1.35 * stages + 0.35) * std::max(1.0, 0.9 * c);
+        slabs = 7.5 + std::max(1.0, 0.8 * w) * (1.454 * stages - 0.387) + 0.73 * mb;
+    }
+    return totals < std::max(slabs, 10.0);
 }
 
 static int launch_ragged_streams(ContractParams &p, void *stream)

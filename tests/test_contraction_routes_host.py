@@ -102,8 +102,8 @@ def refusal(spec, bx, by, cut, dt, out, zstrides=None):
         E.einsum_graph_mark_output(g, z)
         ext = dict(zip(names, tuple(bx) + tuple(by)))
         bz = [ext[l] for l in spec.split("->")[1]]
-        for b, t, st in ((bx, dt, None), (by, dt, None), (bz, out, zstrides)):
-            rels.append(E.tensor_partition(at, t, list(b), [1] * len(b), st))
+        for k, (b, t, st) in enumerate(((bx, dt, None), (by, dt, None), (bz, out, zstrides))):     # (apart from each other)
+            rels.append(E.tensor_partition(at + ((k + 1) << 40), t, list(b), [1] * len(b), st))
         with pytest.raises(E.EgError) as e:
             E.tr_execute(g, rels[:2], rels[2:], at, 1 << 50)
         return str(e.value)
@@ -116,9 +116,9 @@ def refusal(spec, bx, by, cut, dt, out, zstrides=None):
 @pytest.mark.parametrize("dt,out", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "f32")])
 @pytest.mark.parametrize("spec,bx,by,cut,zstrides", [
     ("jab,jk->abk", (130, 13, 79), (130, 1101), {"j": 2}, [82 * 1101, 1101, 1]),          # row labels that do not join in the result
-    ("jab,jk->abk", (1000, 30, 35), (1000, 1101), {"j": 8}, [40 * 1101, 1101, 1]),
+    ("jab,jk->abk", (123, 30, 35), (123, 1101), {"j": 3}, [40 * 1101, 1101, 1]),
     ("ij,jab->iab", (1101, 130), (130, 13, 79), {"j": 2}, [13 * 82, 82, 1]),              # column labels
-    ("bf,bhd->fhd", (1000, 3001), (1000, 5, 77), {"b": 8}, [400, 80, 1]),
+    ("bf,bhd->fhd", (123, 3001), (123, 5, 77), {"b": 3}, [400, 80, 1]),
 ])
 def test_ragged_cut_products_into_strided_results_are_accepted(spec, bx, by, cut, zstrides, dt, out):
     for z in (None, zstrides):

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from tests._parity import RTOL_BF16, RTOL_F32, single_vertex, violations
+from tests.test_gpu_contract_totals import _stages
 from oracle.graph_ref import run_graph
 from synth_inputs.prng import HostTensor, uniform_pm1
 
@@ -78,15 +79,15 @@ def test_blocks_along_the_contracted_label(spec, bx, by, part, dt, odt):
 
 @pytest.mark.parametrize("dt,odt", TYPES)
 @pytest.mark.parametrize("spec,bx,by,pad,joins", [
-    ("ij,jk->ik", (517, 2 * 65), (2 * 65, 643), (0, 21), True),
-    ("jab,jk->abk", (2 * 65, 13, 39), (2 * 65, 643), (0, 3, 0), False),        # row labels that join in a dense result only
-    ("ij,jab->iab", (517, 2 * 65), (2 * 65, 13, 49), (0, 0, 3), False),        # column labels
+    ("ij,jk->ik", (1027, 3 * 41), (3 * 41, 1101), (0, 21), True),
+    ("jab,jk->abk", (3 * 41, 25, 41), (3 * 41, 1101), (0, 3, 0), False),       # row labels that join in a dense result only
+    ("ij,jab->iab", (1027, 3 * 41), (3 * 41, 23, 49), (0, 0, 3), False),       # column labels
 ])
 def test_blocks_into_a_strided_result(spec, bx, by, pad, joins, dt, odt):
     import torch
     print(f"ragged blocks into a strided result {spec} X{bx} Y{by} {dt}->{odt}", flush=True)
     x, y = (HostTensor.from_f32(uniform_pm1(73, p, int(np.prod(b))).reshape(b), dt) for p, b in enumerate((bx, by)))
-    w = single_vertex(spec, x, y, odt, parts={"d": {"j": 2}})
+    w = single_vertex(spec, x, y, odt, parts={"d": {"j": 3}})
     ref = run_graph(w, {"X": x, "Y": y})["Z"].as_f64()
     big = torch.full([n + p for n, p in zip(ref.shape, pad)], 7.0, dtype=torch.float32 if odt == "f32" else torch.bfloat16, device="cuda")
     view = big[tuple(slice(0, n) for n in ref.shape)]
@@ -96,3 +97,15 @@ def test_blocks_into_a_strided_result(spec, bx, by, pad, joins, dt, odt):
     assert bad == 0, f"{bad} elements out of tolerance (worst {worst:.2f}x)"
     view.fill_(7.0)
     assert bool((big == 7.0).all())
+
+
+@pytest.mark.parametrize("spec,bx,by,cut,dt,odt,totals", [
+    ("ji,jk->ik", (16 * 324, 315), (16 * 324, 200), 16, "bf16", "bf16", False),       # 20 tiles: slabs 16.9 us, totals 88.9
+    ("ij,kj->ik", (1871, 3 * 1335), (706, 3 * 1335), 3, "bf16", "f32", False),        # 360 tiles, two rounds: 259 and 300
+    ("ij,jk->ik", (53, 8 * 20), (8 * 20, 999), 8, "bf16", "bf16", False),             # 16 tiles: 9.8 and 13.5
+    ("ij,jk->ik", (2477, 8 * 81), (8 * 81, 1273), 8, "bf16", "bf16", True),           # 780 tiles: 85 and 41
+    ("ij,jk->ik", (3001, 8 * 125), (8 * 125, 1530), 8, "f32", "f32", True),           # 1128 tiles: 287 and 215
+])
+def test_totals_only_where_they_are_faster_than_slabs(spec, bx, by, cut, dt, odt, totals):
+    print(f"ragged totals or slabs {spec} X{bx} Y{by} j cut {cut} {dt}->{odt}", flush=True)
+    assert _stages(spec, bx, by, cut, dt, odt) == (["join"] if totals else ["join", "aggregate"])
