@@ -6,13 +6,14 @@
 // to sixteen iterations, and branches around the loads make the compiler wait for all of them), and feeds it to 16x16x32 MFMAs
 // whose other operand is X, padded to 16 rows by loads outside its descriptor.  No LDS before the end, where the eight waves of a
 // workgroup, which split its part of the contracted label, add their sums in ascending order.  us with Y from memory, aggregation
-// of the pieces included, tiles before: 8 x 4096 x 4096 24.3 -> 14.1 (33.5 MB), 8 x 4096 x 11008 28.4 -> 23.1, 8 x 11008 x 4096
-// 29.9 -> 22.0, 8 x 4096 x 4096 with Y along k 19.3 -> 12.8.
+// of the pieces included, tiles and now: 8 x 4096 x 4096 24.0 and 11.6 (33.5 MB), 8 x 4096 x 11008 30.1 and 22.4 (4.0 TB/s),
+// 8 x (8 x 1376) x 4096 30.8 and 22.7, 8 x 4096 x 4096 with Y along k 23.6 and 10.6.
 //   Y contiguous along its columns: a lane takes VC neighbouring columns of eight consecutive k and turns them around in
 //       registers (v_perm), which gives VC fragments; fragment f of lane c stands for column VC * c + f of the wave's 16 * VC.
-//   Y contiguous along k: a lane's 16 bytes are a fragment already; a wave takes 16 columns and 256 k per iteration.
-// A launch is cut along the contracted label into as many pieces as the vertex has partial slabs, where its columns alone do not
-// give every compute unit a workgroup.
+//   Y contiguous along k: a lane's 16 bytes are a fragment already; a wave takes 16 columns and 128 k per iteration (256 took 155
+//       registers, one workgroup to a compute unit, and launches of a few more than 256 a second round: 8 x 768 x 12160 16.6 -> 12.7).
+// A launch is cut along the contracted label into at most as many pieces as the vertex has partial slabs: so many that the busiest
+// compute unit has the least to fetch (rows_us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -47,14 +48,23 @@ template <bool YK, int VC>
 __global__ __launch_bounds__(kWaves * 64, 2) void k_contract_rows(const ContractParams p)
 {
     fetch_params<sizeof(ContractParams)>();
-    constexpr int COLS = YK ? 16 : 16 * VC, KI = YK ? 256 : 32, NL = 8;      // columns of a workgroup, k of an iteration, loads of Y per iteration
+    constexpr int COLS = YK ? 16 : 16 * VC, KI = YK ? 128 : 32, NL = YK ? 4 : 8;      // columns of a workgroup, k of an iteration, loads of Y per iteration
     constexpr int NX = KI / 32;                                              // fragments of X per iteration
     constexpr int PITCH = COLS + 4;
     __shared__ __attribute__((aligned(16))) float sums[kWaves][16 * PITCH];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, g = lane >> 4;
-    const int64_t n0 = (int64_t)blockIdx.x * COLS;
-    const int32_t piece = blockIdx.y, M = (int32_t)p.M;
+    // Where rows of Y are no whole 128-byte lines, neighbouring strips share lines: they run on one XCD then and find them in its L2
+    // (16 x (4 x 2768) x 8624 82 -> 71 us; with whole lines 34.6 -> 36.0 on 15 x 5544 x 11264, so not there).
+    uint32_t strip = blockIdx.x, part = blockIdx.y;
+    if (p.k_align) {
+        const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x, total = gridDim.x * gridDim.y, per = total / 8, rem8 = total % 8, xcd = id % 8;
+        const uint32_t logical = xcd * per + (xcd < rem8 ? xcd : rem8) + id / 8;
+        part = logical / gridDim.x;
+        strip = logical - part * gridDim.x;
+    }
+    const int64_t n0 = (int64_t)strip * COLS;
+    const int32_t piece = (int32_t)part, M = (int32_t)p.M;
 
     // this wave's k: a part of the piece, whole iterations of 32 (p.k_stages: k per piece)
     const int32_t K = (int32_t)p.K, first = piece * p.k_stages, last = first + p.k_stages < K ? first + p.k_stages : K;
@@ -171,19 +181,42 @@ bool contract_rows_suits(const ContractParams &p)
     const int64_t over = p.K + 2048;
     if (over + span(p.m, p.m.s0) >= (1ll << 30) || over * p.k.s1[0] + span(p.n, p.n.s0) >= (1ll << 30)) return false;
     if (((uintptr_t)p.x & 15) || ((uintptr_t)p.y & 15)) return false;
+    // Y along k: a strip of 16 columns fetches X whole, which is as much again at 16 rows; the tiles stream large matrices of whole
+    // 128-byte lines faster then (16 x 4096 x 14336 34.2 us on the tiles, 39.7 here; 16 x 2560 x 12288 1.14 times faster here, 12 x 4096 x
+    // 8128 1.07, and 16 x 9168 x 12288, whose rows are no whole lines, 1.23; 8 x 8192 x 14336 63.0 and 62.2 from memory, but 42 and 62
+    // where the matrix stays in the last-level cache from call to call)
+    if (p.b_kcontig && p.M > 4 && p.K * p.N > (p.M > 8 ? 40000000 : 80000000) && p.n.s0[p.n.n - 1] % 64 == 0) return false;
     return true;
 }
 
-// How many pieces the contracted label is cut into, of at most `slabs`, so that every compute unit has a workgroup; and so many that
+// us of a launch in so many pieces, beyond what all of them have: the busiest compute unit's share of Y at the rate a unit fetches it
+// (strips of 128 columns keep more in flight than those of 64), or all of it at the memory's; and an aggregation's.  Over 90 shapes of
+// either layout, Y from memory, each in 1 to 8 pieces and with either strip, its choice is 0.3 (0.6) % slower than the best on average
+// and 6 % at most.  (One piece from 160 strips on, 256 workgroups and more below, took 29.7 us for 15 x (4 x 768) x 9240, now 18.8; 31.7 for
+// 8 x 7936 x 6400, now 22.6: workgroups beyond 256 made a second round.)
+static double rows_us(const ContractParams &p, bool wide, int64_t pieces)
+{
+    const int64_t cols = p.b_kcontig ? 16 : wide ? 128 : 64, on_unit = ((p.N + cols - 1) / cols * pieces + 255) / 256;
+    const double unit = p.b_kcontig ? 18e3 : wide ? 28e3 : 20e3, memory = p.b_kcontig ? 4e6 : 6e6;          // bytes per us
+    const double us = std::max((double)p.K * p.N * 2 / memory, (double)(on_unit * cols * 2 * ((p.K + pieces - 1) / pieces)) / unit);
+    return us + (pieces > 1 ? 1.5 + 0.2 * pieces + (double)(p.M * p.N * 4 * pieces) / 2e6 : 0);
+}
+
+static bool rows_wide(const ContractParams &p, int64_t pieces) { return !p.b_kcontig && rows_us(p, true, pieces) < rows_us(p, false, pieces); }
+
+// How many pieces the contracted label is cut into, of at most `slabs` and of 256 elements at least; and so many that
 // no wave sums up more of it than a slab's block does.  0: more than a grid has room for, not for this kernel
 constexpr int kMaxPieces = 65535;
 int contract_rows_pieces(const ContractParams &p, int64_t slabs)
 {
-    const int64_t groups = p.b_kcontig ? (p.N + 15) / 16 : (p.N + 63) / 64;
-    int64_t s = groups >= 160 ? 1 : (256 + groups - 1) / groups;         // (8 x 4096 x 11008: 23.1 us in one piece, 22.4 to 26.4 in 2 to 8 and their aggregation)
-    s = std::min(s, std::min(slabs, p.K / 256));
-    s = std::max<int64_t>(s, (slabs + rows::kWaves - 1) / rows::kWaves);
-    return s <= kMaxPieces ? (int)s : 0;
+    const int64_t least = (slabs + rows::kWaves - 1) / rows::kWaves, most = std::max(least, std::min(slabs, p.K / 256));
+    int64_t best = least;
+    double us = 0;
+    for (int64_t s = least; s <= most && s < least + 16; s++) {
+        const double t = rows_us(p, rows_wide(p, s), s);
+        if (s == least || t < us) { best = s; us = t; }
+    }
+    return best <= kMaxPieces ? (int)best : 0;
 }
 
 int launch_contract_rows(ContractParams &p, int pieces, void *stream)
@@ -191,8 +224,8 @@ int launch_contract_rows(ContractParams &p, int pieces, void *stream)
     if (!p.x || !p.y || !p.out.ptr) return fail(EG_ERR_NULL, "contraction: NULL operand");
     if (!contract_rows_suits(p) || pieces < 1 || pieces > kMaxPieces || (pieces > 1) != (p.out.slab_elems != 0)) return fail(EG_ERR_LIMIT, "contraction: shape not eligible for the few-row kernel");
     p.k_stages = (int32_t)(((p.K + pieces - 1) / pieces + 31) / 32 * 32);
-    // columns per lane: 8, or 4 where that gives too few workgroups
-    const bool wide = (p.N + 127) / 128 * pieces >= 256;
+    p.k_align = !p.b_kcontig && p.k.s1[0] * 2 % 128 != 0;
+    const bool wide = rows_wide(p, pieces);
     const int cols = p.b_kcontig ? 16 : wide ? 128 : 64;
     const dim3 grid((unsigned)((p.N + cols - 1) / cols), (unsigned)pieces), block(rows::kWaves * 64);
     hipStream_t st = (hipStream_t)stream;
