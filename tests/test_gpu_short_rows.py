@@ -45,3 +45,23 @@ def test_short_and_column_reductions_match_the_oracle(spec, bx, by, dx, dy, oplu
         r.close()
     # sums of up to 1001 fp32 products of order one: at most 10 + 3 levels of rounding of 2^-24 of the terms' sum of magnitudes
     assert violations(got, ref, RTOL_F32)[0] == 0
+
+
+@pytest.mark.parametrize("b,j", [(2, 32), (2, 33), (20971, 17), (20972, 17)])
+def test_one_output_per_lane_where_parameters_are_fetched_ahead_and_where_not(b, j):
+    """Up to 32 elements a lane and 524288 lanes, and the first beyond."""
+    import torch
+    from paper_2410_02682_amd.runner import GraphRunner, to_device, to_host
+    print(f"one output per lane {b} x 5 x {j} x 5", flush=True)
+    x, y = (HostTensor.from_f32(uniform_pm1(97, i, int(np.prod(s))).reshape(s), "bf16") for i, s in enumerate(((b, 5, j), (b, j, 5))))
+    w = single_vertex("bij,bjk->bik", x, y, "f32", parts={"d": {}})
+    r = GraphRunner(w, "d")
+    try:
+        assert r.plan("Z")["kernel"] == "generic"
+        r.bind({"X": to_device(x), "Y": to_device(y)})
+        r.run()
+        torch.cuda.synchronize()
+        bad, worst = violations(to_host(r.output("Z")).as_f64(), run_graph(w, {"X": x, "Y": y})["Z"].as_f64(), RTOL_F32)
+        assert bad == 0, f"{bad} elements out of tolerance (worst {worst:.2f}x)"
+    finally:
+        r.close()
