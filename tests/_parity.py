@@ -121,3 +121,23 @@ def magnitudes(w: Workload, inputs: Dict[str, HostTensor]) -> Dict[str, HostTens
         return HostTensor(t.data & np.uint16(0x7FFF), "bf16") if t.dtype == "bf16" else HostTensor(np.abs(t.data), "f32")
 
     return run_graph(wm, {k: absolute(t) for k, t in inputs.items()})
+
+
+def kernel_names(run):
+    """Names of the library's kernels that run() launches, as the profiler records them: which one of several kernels of a kind ran."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        run()
+        torch.cuda.synchronize()
+    return [e.name for e in p.events() if "eg::" in e.name]
+
+
+def same_values(got: np.ndarray, ref: np.ndarray, rtol: float) -> bool:
+    """As `violations`, with infinities and NaN: these in the same places, the rest by the rule."""
+    got, ref = np.asarray(got, dtype=np.float64), np.asarray(ref, dtype=np.float64)
+    if not (np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])):
+        return False
+    fin = np.isfinite(ref)
+    return violations(got[fin], ref[fin], rtol)[0] == 0

@@ -5,7 +5,7 @@ stages per block, several aggregated labels, batch labels, every operand layout,
 import numpy as np
 import pytest
 
-from tests._parity import RTOL_BF16, RTOL_F32, single_vertex, violations
+from tests._parity import RTOL_BF16, RTOL_F32, kernel_names, same_values, single_vertex, violations
 from oracle.graph_ref import run_graph
 from synth_inputs.prng import HostTensor, uniform_pm1
 
@@ -128,5 +128,51 @@ def _stages(spec, bx, by, cut, in_dtype, out_dtype):
         r.run()
         torch.cuda.synchronize()
         return [q["stage"] for q in E.tr_profile_read(r.g)]
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("spec,bx,by,part,stages", [c + ({}, 4) for c in PLAIN] + [(c[0], c[1], c[2], c[3], 2 if c[7] == 4 or i < 10 else 4) for i, c in enumerate(CASES)] + [
+    ("ij,jk->ik", (264, 504), (504, 392), {}, 2),                            # reductions under 512 keep two
+])
+def test_number_of_stages(spec, bx, by, part, stages):
+    """k_contract_dma<tile rows, tile columns, bytes of k, stages, ...>: that the cases above reach the kernel they are about."""
+    import torch
+    from paper_2410_02682_amd.runner import GraphRunner
+    case = next((c for c in CASES if (c[0], c[1], c[2], c[3]) == (spec, bx, by, part)), None)
+    dt = case[4] if case else "bf16"
+    t = torch.float32 if dt == "f32" else torch.bfloat16
+    w = single_vertex(spec, *(HostTensor(np.zeros(b, np.float32 if dt == "f32" else np.uint16), dt) for b in (bx, by)), "f32", parts={"d": part})
+    r = GraphRunner(w, "d", contract=dict(kernel="dma", waves=case[7] if case else 0))
+    try:
+        r.bind({n: torch.zeros(b, dtype=t, device="cuda") for n, b in (("X", bx), ("Y", by))})
+        names = kernel_names(r.run)
+        assert len(names) == 1 and f"k_contract_dma<128, 128, 128, {stages}," in names[0], names
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("part", [{}, {"j": 2}])
+@pytest.mark.parametrize("spec", ["ij,jk->ik", "ij,kj->ik"])
+def test_infinities_and_nan_with_four_stages(spec, part):
+    """Zeros behind the last stage and the exchange between the two groups of waves leave other rows and columns alone."""
+    import torch
+    from paper_2410_02682_amd.runner import GraphRunner
+    gen = torch.Generator().manual_seed(7)
+    bx, by = (392, 1096), (1096, 264) if spec == "ij,jk->ik" else (264, 1096)
+    x, y = (torch.empty(b).uniform_(0.5, 1.0, generator=gen).bfloat16() for b in (bx, by))
+    yt = y if spec == "ij,jk->ik" else y.t()
+    yt[0, 7], yt[1095, 130], yt[600, 263] = float("inf"), float("nan"), float("-inf")
+    x[5, 1000], x[391, 17], x[64, 3] = float("-inf"), float("nan"), 0.0
+    yt[3, 100] = float("inf")
+    ref = x.double() @ yt.double()
+    w = single_vertex(spec, HostTensor(np.zeros(bx, np.uint16), "bf16"), HostTensor(np.zeros(by, np.uint16), "bf16"), "f32", parts={"d": part})
+    r = GraphRunner(w, "d", contract=dict(kernel="dma"), tiled_partials=True)
+    try:
+        r.bind({"X": x.cuda(), "Y": y.cuda()})
+        names = kernel_names(r.run)
+        if not part:
+            assert "k_contract_dma<128, 128, 128, 4," in names[0], names
+        assert same_values(r.output("Z").cpu().numpy(), ref.numpy(), RTOL_F32)
     finally:
         r.close()

@@ -4,7 +4,7 @@ matrix, cuts of every label, results in either dtype.  Against the oracle, with 
 import numpy as np
 import pytest
 
-from tests._parity import RTOL_BF16, RTOL_F32, single_vertex, violations
+from tests._parity import RTOL_BF16, RTOL_F32, kernel_names, same_values, single_vertex, violations
 from oracle.graph_ref import run_graph
 from synth_inputs.prng import HostTensor, uniform_pm1
 
@@ -88,3 +88,52 @@ def test_pieces_replace_the_blocks_unless_the_slabs_are_asked_for(spec, bx, by, 
             assert bad == 0, f"tiled {tiled}: {bad} elements out of tolerance (worst {worst:.2f}x)"
         finally:
             r.close()
+
+
+def _zeros(spec, bx, by, part, out_dtype):
+    import torch
+    from paper_2410_02682_amd.runner import GraphRunner
+    x, y = (HostTensor(np.zeros(b, np.uint16), "bf16") for b in (bx, by))
+    r = GraphRunner(single_vertex(spec, x, y, out_dtype, parts={"d": part}), "d")
+    r.bind({n: torch.zeros(b, dtype=torch.bfloat16, device="cuda") for n, b in (("X", bx), ("Y", by))})
+    return r
+
+
+@pytest.mark.parametrize("spec,bx,by,part,out_dtype,rows", [c[:5] + (c[1][0] <= 16,) for c in CASES] + [
+    ("ij,kj->ik", (8, 4096), (10240, 4096), {}, "bf16", True),
+    ("ij,kj->ik", (9, 4096), (10240, 4096), {}, "bf16", False),              # a large matrix along k under more than eight rows
+    ("ij,kj->ik", (9, 4104), (10240, 4104), {}, "bf16", True),               # whose rows are no whole 128-byte lines
+    ("ij,kj->ik", (5, 8192), (10240, 8192), {}, "bf16", False),
+    ("ij,kj->ik", (4, 8192), (10240, 8192), {}, "bf16", True),
+])
+def test_which_products_run_on_the_few_row_kernel(spec, bx, by, part, out_dtype, rows):
+    r = _zeros(spec, bx, by, part, out_dtype)
+    try:
+        names = kernel_names(r.run)
+        assert any("k_contract_rows" in n for n in names) == rows, names
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("spec,bx,by", [("ij,jk->ik", (3, 520), (520, 200)), ("ij,jk->ik", (5, 264), (264, 33000)), ("ij,kj->ik", (7, 520), (200, 520))])
+def test_infinities_and_nan_stay_where_they_belong(spec, bx, by):
+    """The rows up to 16 and the elements behind the last k that the kernel adds are zeros, and no other column is touched."""
+    import torch
+    from paper_2410_02682_amd.runner import GraphRunner
+    gen = torch.Generator().manual_seed(5)
+    x, y = (torch.empty(b).uniform_(0.5, 1.0, generator=gen).bfloat16() for b in (bx, by))
+    yt = y if spec == "ij,jk->ik" else y.t()
+    yt[0, 7], yt[-1, 8], yt[300 % yt.shape[0], 190] = float("inf"), float("nan"), float("-inf")
+    x[1, 100] = float("inf")
+    x[2, 3] = 0.0
+    yt[3, 100] = float("inf")                                                # 0 times an infinity
+    ref = x.double() @ yt.double()
+    w = single_vertex(spec, HostTensor(np.zeros(bx, np.uint16), "bf16"), HostTensor(np.zeros(by, np.uint16), "bf16"), "f32", parts={"d": {}})
+    r = GraphRunner(w, "d")
+    try:
+        r.bind({"X": x.cuda(), "Y": y.cuda()})
+        names = kernel_names(r.run)
+        assert any("k_contract_rows" in n for n in names), names
+        assert same_values(r.output("Z").cpu().numpy(), ref.numpy(), RTOL_F32)
+    finally:
+        r.close()
