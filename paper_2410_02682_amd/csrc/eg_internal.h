@@ -255,6 +255,7 @@ int launch_aggregate_tiles(AggTilesParams &p, void *stream);
 bool contract_takes_dma(const ContractParams &p);                              // launch_contract will hand p to the direct-to-LDS kernel
 void contract_dma_variant(const ContractParams &p, int &tm, int &tn, int &nw, int &ns);   // ... which will run this tile shape, wave count and number of stages
 bool contract_ragged_streams(const ContractParams &p);                         // ragged operands that the kernel with branch-free loads takes
+bool contract_ragged_short(const ContractParams &p, double tiles);             // ... but not so short reductions under so many tiles
 bool contract_ragged_totals_pay(const ContractParams &p, int64_t n_agg, int out_bytes);   // the same for ragged products
 bool contract_rows_suits(const ContractParams &p);                             // few rows, streamed operand: see k_contract_rows.hip
 int contract_rows_pieces(const ContractParams &p, int64_t slabs);

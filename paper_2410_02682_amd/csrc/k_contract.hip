@@ -773,6 +773,17 @@ bool contract_ragged_streams(const ContractParams &p)
     return (p.a_kcontig || (p.m.n == 1 && p.M >= epc)) && (p.b_kcontig || (p.n.n == 1 && p.N >= epc));
 }
 
+// A reduction of a stage or two under more tiles than run at once: the loads that the kernel above keeps in flight have nothing to run
+// ahead of, and the tiles with run-by-run loads, of which more fit a compute unit, are faster (us there and here: 5101 x 31 x 3801 to
+// bf16 36 and 43, x 97 48 and 47; bf16 to fp32 x 33 64 and 90, x 97 118 and 134, x 127 136 and 134, 2001 x 33 x 1403 14.4 and 17.7; fp32 x 33
+// 72 and 79, x 63 90 and 88).
+bool contract_ragged_short(const ContractParams &p, double tiles)
+{
+    if (p.n_totals > 1) return false;
+    if (!p.wide) return p.K <= 64 && tiles > 1024;
+    return p.K <= (p.in_dtype == EG_BF16 ? 112 : 72) && tiles > 512;
+}
+
 // Do they run faster with a tile's blocks one after another in one workgroup than each with its own, slabs and an aggregation?  Both
 // ways in us, by rounds of 256 tiles (of two and three workgroups on a compute unit a round costs 0.8 to 0.9) and stages, with what a
 // block costs that is walked over, and the slabs' way through memory at some 1.6 TB/s (they are small); two launches take 10 us at the
@@ -1155,7 +1166,7 @@ bool contract_takes_dma(const ContractParams &p)
 // registers of a 128 x 128 tile's lanes, and with one wave per SIMD left, or two of half the tile, nothing hides the loads
 // (4001 x 3001 x 4099: 447 us with 64 x 64, 557 with 128 x 64, 592 with 128 x 128; 439 with 128 x 128 and plain fp32 sums).
 // Operands of one run each take k_contract_ragged; the forms with run-by-run loads are left for the others (two contracted labels that
-// do not join, runs of a few elements).  Against one output per lane, which ran such shapes before there were tiles: fp32
+// do not join, runs of a few elements) and for short reductions under many tiles.  Against one output per lane, which ran such shapes before there were tiles: fp32
 // 1121 x 319 x 646 371 us, 20 now; a classifier's step of 1000 x 3001 x 1530 x 1003 23.5 ms, 0.50 now.
 static int launch_ragged(ContractParams &p, void *stream)
 {
@@ -1165,7 +1176,7 @@ static int launch_ragged(ContractParams &p, void *stream)
         if (p.in_dtype == EG_BF16) return launch_alu_ops<Cfg<128, 128, 64, 64, true, true>>(p, stream);
         return launch_alu_ops<Cfg<128, 128, 64, 64, false, true>>(p, stream);
     }
-    if (contract_ragged_streams(p)) {
+    if (contract_ragged_streams(p) && !contract_ragged_short(p, (double)(p.n_tuples * p.n_batch * ((p.M + 63) / 64) * ((p.N + 63) / 64)))) {
         if (!p.wide && p.in_dtype != EG_BF16) return fail(EG_ERR_LIMIT, "contraction: ragged fp32 operands are summed in 64 bits");
         return launch_ragged_streams(p, stream);
     }

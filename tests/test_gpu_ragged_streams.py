@@ -4,7 +4,7 @@ contracted label that one workgroup walks over (no aggregation launch; totals in
 import numpy as np
 import pytest
 
-from tests._parity import RTOL_BF16, RTOL_F32, single_vertex, violations
+from tests._parity import RTOL_BF16, RTOL_F32, kernel_names, single_vertex, violations
 from tests.test_gpu_contract_totals import _stages
 from oracle.graph_ref import run_graph
 from synth_inputs.prng import HostTensor, uniform_pm1
@@ -109,3 +109,27 @@ def test_blocks_into_a_strided_result(spec, bx, by, pad, joins, dt, odt):
 def test_totals_only_where_they_are_faster_than_slabs(spec, bx, by, cut, dt, odt, totals):
     print(f"ragged totals or slabs {spec} X{bx} Y{by} j cut {cut} {dt}->{odt}", flush=True)
     assert _stages(spec, bx, by, cut, dt, odt) == (["join"] if totals else ["join", "aggregate"])
+
+
+@pytest.mark.parametrize("dt,odt,m,n,k,streams", [
+    ("bf16", "bf16", 2051, 2051, 64, False), ("bf16", "bf16", 2051, 2051, 65, True), ("bf16", "bf16", 2045, 2047, 64, True),     # 1089 tiles, 1024
+    ("bf16", "f32", 1473, 1409, 112, False), ("bf16", "f32", 1473, 1409, 113, True), ("bf16", "f32", 1471, 1407, 112, True),     # 576, 506
+    ("f32", "f32", 1473, 1409, 72, False), ("f32", "f32", 1473, 1409, 73, True), ("f32", "f32", 1471, 1407, 72, True),
+])
+def test_short_reductions_under_many_tiles(dt, odt, m, n, k, streams):
+    """They take the tiles with run-by-run loads; either way the values are right."""
+    import torch
+    from paper_2410_02682_amd.runner import GraphRunner, to_device, to_host
+    print(f"short ragged {m} x {k} x {n} {dt}->{odt}", flush=True)
+    x, y = (HostTensor.from_f32(uniform_pm1(103, p, int(np.prod(b))).reshape(b), dt) for p, b in enumerate(((m, k), (k, n))))
+    w = single_vertex("ij,jk->ik", x, y, odt, parts={"d": {}})
+    r = GraphRunner(w, "d")
+    try:
+        r.bind({"X": to_device(x), "Y": to_device(y)})
+        names = kernel_names(r.run)
+        assert len(names) == 1 and ("k_contract_ragged" in names[0]) == streams, names
+        ref = (torch.from_numpy(x.as_f64()) @ torch.from_numpy(y.as_f64())).numpy()
+        bad, worst = violations(to_host(r.output("Z")).as_f64(), ref, RTOL_BF16 if odt == "bf16" else RTOL_F32)
+        assert bad == 0, f"{bad} elements out of tolerance (worst {worst:.2f}x)"
+    finally:
+        r.close()
