@@ -31,11 +31,15 @@ DEFAULT_PART = {1: "d222", 2: "mix", 3: "batch8", 4: "heads8", 5: "k16", 6: "spl
 # file, scaled by what the same counters read for the plain 1 GiB copy kernel (see profiles/); a family that is not listed
 # reports null.  Keys: (workload, partitioning, kernel family).
 MEASURED_TRAFFIC = {
+    ("c2", "mix", "contract_mfma"): 2362970210,    # 1805 MiB fetched + 448 MiB written per launch (the first block's sums of every tile go out and come back: 256 MiB each way)
+    ("c3", "batch8", "contract_mfma"): 327808563,  # 268 MiB fetched + 45 MiB written (mean over the step's five contractions)
+    ("c4", "heads8", "contract_mfma"): 1131486662, # 877 MiB fetched + 202 MiB written (mean over the step's nine contractions)
+    ("c5", "k16", "contract_mfma"): 41641456143,   # 38 689 MiB fetched (L2 misses; the Infinity Cache serves the re-reads) + 1023 MiB written
     ("c3", "batch8", "map"): 83944448,             # 48 MiB fetched + 32 MiB written (mean over the ReLU and its gradient; the other maps run inside the softmax pass)
     ("c3", "batch8", "softmax_fused"): 51062784,   # 24.7 MiB fetched (logits and labels) + 24 MiB written (log-probabilities and the gradient dL)
     ("c3", "batch8", "reduce_row"): 25293930,      # 24 MiB fetched
     ("c4", "heads8", "softmax_fused"): 2281005450, # 1152 MiB fetched (scores + the mask rows) + 1023 MiB written
-    ("c4", "heads8", "map"): 549389600,            # 352 MiB fetched + 172 MiB written
+    ("c4", "heads8", "map"): 541023616,            # 344 MiB fetched + 172 MiB written
 }
 
 
@@ -145,7 +149,7 @@ def ceilings():
     return out
 
 
-KERNEL_TEXT = {"contract_mfma": "k_contract_dma / k_contract (block contraction on MFMA, all tuples of a vertex per launch)",
+KERNEL_TEXT = {"contract_mfma": "k_contract_dma / k_contract / k_contract_ragged / k_contract_rows (block contraction on MFMA, all tuples of a vertex per launch)",
                "aggregate": "k_aggregate_patches (tile-ordered partial slabs) / k_aggregate_vec4 (dense ones)", "map": "k_map", "reduce_row": "k_reduce_row", "generic": "k_generic",
                "contract_alu": "k_contract_alu (contraction-shaped vertex with another scalar function, vector ALU)",
                "softmax_fused": "k_softmax_rows / k_softmax_rows_bf16 (softmax chain, the sum in front and the element-wise vertices behind it in one pass per row)",
