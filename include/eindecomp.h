@@ -311,7 +311,8 @@ int tr_profile_get(eg_graph *g, int i, int *vertex, int *stage, int *kernel, flo
 
 /* Recorded launch i: the number of fp32 partial slabs it wrote (a join kernel whose vertex has a partitioned aggregated
  * label, or whose reduction the execution cut further) or read (an aggregation); 0 for a join kernel that wrote its
- * vertex's tensor directly.  With the vertex's bound this gives the bytes the launch moved.  *slabs: host. */
+ * vertex's tensor directly.  With the vertex's bound this gives the bytes the launch moved.  (Two long blocks on one kernel call:
+ * the first one's sums wait in the workspace for the second's, one slab written and read again; reported as 0.)  *slabs: host. */
 int tr_profile_get_slabs(eg_graph *g, int i, int64_t *slabs);
 
 /* ---- Choosing the partitioning vectors: EinDecomp (Sections 6-8 of the paper) ------------------------------

@@ -6,6 +6,7 @@
 //     or 256 x 128 tiles with 4 waves of the same 128x64 patch, stages half as deep and two workgroups per compute unit,
 //     so that one workgroup's epilogue, addressing and first loads run under the other's MFMAs;
 //     or 128 x 128 tiles with 4 waves and two workgroups per compute unit when large tiles would leave the chip idle;
+//     or, where a compute unit has one such tile at most, 128 x 128 with 8 waves in two groups of four and one workgroup per unit;
 //   * persistent workgroups, each walking over its share of the output tiles;
 //   * every 16-byte chunk of both operand tiles travels global memory -> LDS directly; the chunk a lane
 //     fetches is chosen so that the contiguous 1 KiB an instruction deposits is already the swizzled layout;
@@ -14,7 +15,10 @@
 //   * an operand contiguous along K sits in LDS as [row][128 bytes of k] and is read with 16-byte reads; an operand
 //     contiguous along M or N sits as [k][TS mn] and is read with the 16-bit transposing LDS read (bf16), which
 //     hands every lane four consecutive k for its own column, or with four 4-byte reads (fp32);
-//   * two LDS stages: the loads of stage t+1 are in flight while the MFMAs of stage t run.
+//   * two LDS stages: the loads of stage t+1 are in flight while the MFMAs of stage t run (256 x 128 tiles three, the eight-wave
+//     128 x 128 tile four: two and three stages in flight);
+//   * what becomes of the blocks along aggregated labels is a template parameter: partial slabs, totals in registers (128 x 128), or
+//     a first block's sums that wait in memory for the second's (256 x 256);
 //   * the loads are buffer loads with a 2 GiB descriptor: a lane whose chunk lies beyond K in the last,
 //     partial stage is given an offset outside the descriptor, fetches nothing and deposits zeros.
 // Several K labels: every run of the innermost one starts a stage of its own (a run of 96 k is a full stage and
@@ -218,19 +222,21 @@ struct TileInfo {
 //   256 x 256, KB = 128, NW = 4: one wave per SIMD, each owning 128 x 128 (two thirds of the LDS read traffic, nothing to
 //       cover a wave's own waits); kept for comparison.
 //   128 x 128, KB = 128, NW = 4: patches of 64 x 64, 78 KiB of LDS, two workgroups per compute unit.  For launches with too
-//       few larger tiles to fill the chip.
+//       few larger tiles to fill the chip, and for totals in registers.
+//   128 x 128, KB = 128, NW = 8, four stages: two groups of four waves, each with patches of 64 x 64 over the whole tile and half
+//       of a stage's k-steps, 132 KiB of LDS, one workgroup per compute unit.  For launches of one tile per compute unit.
 //
 // The kernel is persistent: the workgroups of a compute unit walk over their share of the tiles.  While a tile's
 // epilogue runs, the first two stages of the workgroup's next tile are already on their way into LDS, and the
 // next tile's addressing was worked out while the current tile waited for its own first stage.
 // LDS of one workgroup: the stages, two sets of Z offset tables, the waves' epilogue staging rows
-// (with three stages the staging rows lie in the third stage's buffer, which is free while an epilogue runs)
+// (with three or four stages the staging rows lie in the last stage's buffer, which is free while an epilogue runs)
 constexpr int lds_bytes(int TM, int TN, int KB, int WM, int NW, int NS)
 {
     return NS * (TM + TN) * KB + 2 * (TM + TN) * 8 + (NS == 2 ? NW * 8 * (32 * (TN / (NW / WM) / 32) * 4 + 32) : 0);          // (NS = 4: staging in a stage's buffer)
 }
 
-// NS: LDS stages (2 or 3); REM: the stage count modulo NS.
+// NS: LDS stages (2, 3 or 4); REM: the stage count modulo NS (NS = 4: not used, 0).
 // MODE 1: one tile over n_totals blocks, whose totals stay in registers; 2: as 0, but a tile's two
 // blocks follow one another and the first one's sums wait in memory (p.carry) for the second.
 // Four stages (KG = 2): two groups of waves share the tile, each takes half of a stage's k-steps.
@@ -249,7 +255,7 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
     constexpr int TBL = (TM + TN) * 8;                // one set of Z offset tables (TM rows, TN columns)
     static_assert(KS == 4 || KS == 2, "a stage is four or two k-steps");
     constexpr int CW = 32 * NT, PITCH = CW * 4 + 32, WBUF = 8 * PITCH;   // epilogue staging: 8 rows of a wave's patch
-    // Separate LDS objects for the two stages and for the epilogue: the compiler can then tell that the fragment
+    // Separate LDS objects for the stages and for the epilogue: the compiler can then tell that the fragment
     // reads of one stage, or the epilogue's staging, never alias the direct loads in flight into another object,
     // and does not wait for them.
     __shared__ __attribute__((aligned(1024))) char lds0[STAGE_BYTES];
@@ -440,7 +446,7 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
     };
     const char *ga2, *gb2;
     int kr2, km2;
-    // per-lane addressing of tile t, then its first two stages on their way (both LDS stages must be free)
+    // per-lane addressing of tile t, then its first two stages on their way, of four stages three (their LDS buffers must be free)
     auto start_tile = [&](const TileInfo &t) {
         sa.init(p.m, t.m0, p.M, t.ox0, p.k.s0[kin], wave, lane);
         sb.init(p.n, t.n0, p.N, t.oy0, p.k.s1[kin], wave, lane);
@@ -617,7 +623,7 @@ __global__ __launch_bounds__(NW * 64, 2 * lds_bytes(TM, TN, KB, WM, NW, NS) <= 1
                     acc[i][j][r] = 0.f;
                     if constexpr (TOT) tot[i][j][r] = -0.f;     // the one value that leaves any first sum as it is
                 }
-        __builtin_amdgcn_s_waitcnt(0x0F70);           // the first two stages (and the previous tile's stores) are done
+        __builtin_amdgcn_s_waitcnt(0x0F70);           // the stages that start_tile issued (and the previous tile's stores) are done
         __syncthreads();
         if constexpr (NS == 3) {
             // the last buffer held the previous tile's staging rows until this barrier: its stage goes out now
