@@ -192,29 +192,36 @@ bool contract_rows_suits(const ContractParams &p)
 // us of a launch in so many pieces, beyond what all of them have: the busiest compute unit's share of Y at the rate a unit fetches it
 // (strips of 128 columns keep more in flight than those of 64), or all of it at the memory's; and an aggregation's.  Over 90 shapes of
 // either layout, Y from memory, each in 1 to 8 pieces and with either strip, its choice is 0.3 (0.6) % slower than the best on average
-// and 6 % at most.  (One piece from 160 strips on, 256 workgroups and more below, took 29.7 us for 15 x (4 x 768) x 9240, now 18.8; 31.7 for
+// and 6 % at most; of up to 64 pieces (65536 and 100352 by 64 to 320) the aggregation takes little more than of eight.  (One piece from 160 strips on, 256 workgroups and more below, took 29.7 us for 15 x (4 x 768) x 9240, now 18.8; 31.7 for
 // 8 x 7936 x 6400, now 22.6: workgroups beyond 256 made a second round.)
 static double rows_us(const ContractParams &p, bool wide, int64_t pieces)
 {
     const int64_t cols = p.b_kcontig ? 16 : wide ? 128 : 64, on_unit = ((p.N + cols - 1) / cols * pieces + 255) / 256;
     const double unit = p.b_kcontig ? 18e3 : wide ? 28e3 : 20e3, memory = p.b_kcontig ? 4e6 : 6e6;          // bytes per us
     const double us = std::max((double)p.K * p.N * 2 / memory, (double)(on_unit * cols * 2 * ((p.K + pieces - 1) / pieces)) / unit);
-    return us + (pieces > 1 ? 1.5 + 0.2 * pieces + (double)(p.M * p.N * 4 * pieces) / 2e6 : 0);
+    return us + (pieces > 1 ? 1.5 + 0.2 * std::min<int64_t>(pieces, 8) + 0.02 * pieces + (double)(p.M * p.N * 4 * pieces) / 2e6 : 0);
 }
 
 static bool rows_wide(const ContractParams &p, int64_t pieces) { return !p.b_kcontig && rows_us(p, true, pieces) < rows_us(p, false, pieces); }
 
 // How many pieces the contracted label is cut into, of at most `slabs` and of 256 elements at least; and so many that
 // no wave sums up more of it than a slab's block does.  0: more than a grid has room for, not for this kernel
-constexpr int kMaxPieces = 65535;
+constexpr int64_t kMaxPieces = 65535;
 int contract_rows_pieces(const ContractParams &p, int64_t slabs)
 {
-    const int64_t least = (slabs + rows::kWaves - 1) / rows::kWaves, most = std::max(least, std::min(slabs, p.K / 256));
+    const int64_t least = (slabs + rows::kWaves - 1) / rows::kWaves, most = std::max(least, std::min(std::min(slabs, p.K / 256), kMaxPieces));
     int64_t best = least;
-    double us = 0;
-    for (int64_t s = least; s <= most && s < least + 16; s++) {
-        const double t = rows_us(p, rows_wide(p, s), s);
-        if (s == least || t < us) { best = s; us = t; }
+    double us = -1;
+    for (int w = 0; w < (p.b_kcontig ? 1 : 2); w++) {
+        // the fewest, and of all numbers that give the busiest unit the same number of workgroups the largest
+        const int64_t cols = p.b_kcontig ? 16 : w ? 128 : 64, strips = (p.N + cols - 1) / cols;
+        int64_t s = least;
+        for (int64_t u = (strips * least + 255) / 256, tries = 0; tries < 16; u++, tries++) {
+            const double t = rows_us(p, w != 0, s);
+            if (us < 0 || t < us) { best = s; us = t; }
+            if (s == most) break;
+            s = std::min(std::max(256 * u / strips, s), most);
+        }
     }
     return best <= kMaxPieces ? (int)best : 0;
 }
