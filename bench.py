@@ -262,7 +262,8 @@ def measure(config, pname, steps, warmup, fuse_aggregation=False, contract=None,
         else:
             k.update({"bound": "hbm", "achieved": f["bytes"] / (f["ms"] * 1e-3) / 1e9, "peak": PEAK_HBM_GBS, "unit": "GB/s"})
         k["frac"] = k["achieved"] / k["peak"]
-        t = MEASURED_TRAFFIC.get((f"c{config}", pname, key))
+        # counted on the default path: an alternative's launches of the same family are others
+        t = None if fuse_aggregation or fuse_attention or dense_partials or contract else MEASURED_TRAFFIC.get((f"c{config}", pname, key))
         k["traffic"] = t
         kernels[key] = k
     # The same steps once more as replays of captured HIP graphs (one graph per buffer set; tr_execute only enqueues
