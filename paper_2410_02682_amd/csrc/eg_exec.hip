@@ -369,10 +369,10 @@ static double untiled_us(const Routed &r, const ContractParams &c, int64_t n_tup
     const bool bf = c.in_dtype == EG_BF16, mul = c.otimes == EG_MUL;
     const double outs = (double)(c.M * c.N * c.n_batch * n_tuples), work = outs * c.K * 1e-6;
     if (r.kind != EG_KERNEL_REDUCE_ROW) return 5 + std::max(c.K * (bf ? 0.37 : 0.22), work / 0.8);       // a lane walks all of K
-    if (r.rp.col && (!mul || c.n_batch > 1)) return 5.5 + std::max(0.07 * std::min<int64_t>(c.K, 150), work / 0.9);
-    if (r.rp.col) {                                           // (121 shapes of 17 to 1200 rows and columns, no batches; 129 x 321 x 72 6.7 us, on tiles 12.4)
+    if (r.rp.col && (!mul || (c.n_batch > 1 && c.N < 16))) return 5.5 + std::max(0.07 * std::min<int64_t>(c.K, 150), work / 0.9);
+    if (r.rp.col) {                                           // (320 shapes of 9 to 1200 rows and columns, 200 with a batch; 129 x 321 x 72 6.7 us, on tiles 12.4)
         const double cut = r.rp.split > 1 ? 1 : 0;            // an aggregation behind it
-        return cut + (bf ? 3.75 + std::max(0.02 * std::min<int64_t>(c.K, 300), work / 3.2) : 3.5 + 0.04 * std::min<int64_t>(c.K, 200) + work / 5 + outs * 1.2e-5);
+        return cut + (bf ? 3.75 + std::max(0.02 * std::min<int64_t>(c.K, 300), work / 3.2) + outs * 2e-6 : 3.5 + 0.04 * std::min<int64_t>(c.K, 200) + work / 5 + outs * 1.2e-5);
     }
     if (r.rp.vec == 8) return 0;                              // 16-byte loads along the reduction: not measured, as before there were tiles
     // a wave per output; an operand that is not contiguous along K comes a line per element once it is larger than an XCD's cache

@@ -68,6 +68,7 @@ def test_walking_blocks_as_one_index_space_takes_no_more_slabs(spec, bx, by, cut
     # columns in whole vectors: a column reduction (129 x 321 x 72 6.7 us, on tiles 12.4; 119 x 62 x 336 4.6 and 8.3)
     ("ji,jk->ik", (129, 321), (129, 72), "bf16", "f32", "reduce_row", 1),
     ("ij,jk->ik", (119, 62), (62, 336), "bf16", "f32", "reduce_row", 1),
+    ("bij,bjk->bik", (32, 11, 82), (32, 82, 16), "f32", "f32", "reduce_row", 1),           # 7.3 and 8.9
     # tiles that would be almost empty
     ("bij,bjk->bik", (100000, 5, 17), (100000, 17, 5), "bf16", "f32", "generic", 1),
     # full ones, however short or long the reduction
